@@ -37,6 +37,11 @@ __device__ __forceinline__ void dma16_sv(const char* sbase, uint32_t voff, bf16_
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
                : "memory", "m0");
 }
+// The same from a 64-bit address of the lane's own.
+__device__ __forceinline__ void dma16_v(const char* src, bf16_t* dst) {
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(dst);
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 template <int BK>
@@ -96,6 +101,26 @@ __device__ __forceinline__ void sched_step() {
       __builtin_amdgcn_sched_group_barrier(0x008, NMF - (NR + 1) / 2 - 1, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// f(std::integral_constant<int, 0>) .. f(std::integral_constant<int, N - 1>)
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// f(std::integral_constant<int, k>) with k = n clamped to [2, N]
+template <int N, class F>
+__device__ __forceinline__ void with_phases(int n, F&& f) {
+  if constexpr (N == 2) {
+    f(std::integral_constant<int, 2>{});
+  } else {
+    if (n >= N) f(std::integral_constant<int, N>{});
+    else with_phases<N - 1>(n, f);
+  }
 }
 
 // f(std::integral_constant<int, k>) with k = min(n, N) (n >= 0)
