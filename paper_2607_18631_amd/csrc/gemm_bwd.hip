@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemm_bwd_tiles.hpp"
 #include "gemm_device.hpp"
 #include "kernels.hpp"
 
@@ -52,11 +53,6 @@ __device__ __forceinline__ bf16x8 tr_pair(const bf16_t* p0, const bf16_t* p1) {
   const v8s c = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, c);
 }
-
-// One tile: output rows [m0, m_end) x columns [n0, N) of group g, K range [kbeg, kbeg + klen).
-struct BTile {
-  int g, m0, m_end, n0, kbeg, klen;
-};
 
 // Copies of one operand's slice (R tile rows x BK) into its LDS block, over NW waves.
 // MN = false: global (r, k) at base + r * ld + k; MN = true: global (k, r) at base + k * ld + r.
@@ -163,80 +159,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_bwd(GemmBwdProblem
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int groups = p.groups;
   const int tn = (p.N + BN - 1) / BN;
 
-  // segment table: begin / length of every group (clamped to the row bound)
-  const int cap = (int)p.max_rows;
-  for (int g = tid; g < groups; g += NTH) {
-    int b, e;
-    if (p.seg_stride > 0) {
-      b = g * p.seg_stride;
-      e = b + min(max(p.offsets[g], 0), p.seg_stride);
-    } else {
-      b = min(max(p.offsets[g], 0), cap);
-      e = min(max(p.offsets[g + 1], b), cap);
-    }
-    s_off[g] = b;
-    s_len[g] = e - b;
-  }
-  __syncthreads();
-  int total;
-  if constexpr (MODE == BWD_ROWS) {
-    // tiles per group = ceil(len / BM) * tn, prefix-summed into s_tp (first tile of g)
-    constexpr int PER = (kMaxGroups + NTH - 1) / NTH;
-    int loc[PER], lsum = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int g = tid * PER + i;
-      loc[i] = g < groups ? ((s_len[g] + BM - 1) / BM) * tn : 0;
-      lsum += loc[i];
-    }
-    int excl;
-    total = block_exclusive_scan<NTH>(lsum, s_tmp, excl);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int g = tid * PER + i;
-      if (g < groups) s_tp[g] = excl;
-      excl += loc[i];
-    }
-    if (tid == 0) s_tp[groups] = total;
-    __syncthreads();
-  } else {
-    total = groups * ((p.M + BM - 1) / BM) * tn;
-  }
-
-  auto decode = [&](int tile) -> BTile {
-    BTile t;
-    if constexpr (MODE == BWD_ROWS) {
-      int lo = 0, hi = groups;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_tp[mid] <= tile) lo = mid; else hi = mid;
-      }
-      t.g = __builtin_amdgcn_readfirstlane(lo);
-      const int local = tile - __builtin_amdgcn_readfirstlane(s_tp[t.g]);
-      const int len = __builtin_amdgcn_readfirstlane(s_len[t.g]);
-      const int tm = (len + BM - 1) / BM;
-      const int mi = local % tm, ni = local / tm;         // m-fastest: tiles of one weight panel adjacent
-      const int b = __builtin_amdgcn_readfirstlane(s_off[t.g]);
-      t.m0 = b + mi * BM;
-      t.m_end = b + len;
-      t.n0 = ni * BN;
-      t.kbeg = 0;
-      t.klen = p.K;
-    } else {
-      const int tm = (p.M + BM - 1) / BM;
-      t.g = tile / (tm * tn);
-      const int local = tile - t.g * tm * tn;
-      t.m0 = (local % tm) * BM;
-      t.m_end = p.M;
-      t.n0 = (local / tm) * BN;
-      t.kbeg = __builtin_amdgcn_readfirstlane(s_off[t.g]);
-      t.klen = __builtin_amdgcn_readfirstlane(s_len[t.g]);
-    }
-    return t;
-  };
+  const int total = bwd_tile_table<MODE, NTH, BM>(p, tn, s_off, s_len, s_tp, s_tmp);
+  auto decode = [&](int tile) { return bwd_decode<MODE, BM, BN>(p, tile, tn, s_off, s_len, s_tp); };
 
   CX cx;
   CW cw;
@@ -539,38 +465,23 @@ hipError_t launch_gemm_bwd(const GemmBwdProblem& p, hipStream_t stream) {
     auto rounds = [&](double tiles) { return std::max(1.0, std::ceil(tiles / cus - 0.05)); };
     const double tn256 = (double)((p.N + 255) / 256), tn128 = (double)((p.N + 127) / 128);
     const double c1 = rounds(mtiles(256) * tn256), c2 = 0.6 * rounds(mtiles(256) * tn128);
-    const double c3 = kt ? 1e30 : 1.15 * rounds(mtiles(320) * tn256);   // no tail instance of it
-    int cfg = (c3 < c1 && c3 <= c2) ? 3 : c2 < c1 ? 2 : 1;
-#ifdef MOE_BWD_ROWS_CFG
-    cfg = MOE_BWD_ROWS_CFG;
-#endif
-    if (cfg == 3 && !kt) return launch_bwd<320, 256, 64, 2, 2, 4, false, true, BWD_ROWS, 1, false>(p, stream);
+    const double c3 = 1.15 * rounds(mtiles(320) * tn256);
+    const int cfg = (c3 < c1 && c3 <= c2) ? 3 : c2 < c1 ? 2 : 1;
+    if (cfg == 3) return launch_phase_bwd(320, p, stream);
     if (cfg == 2)
       return kt ? launch_bwd<256, 128, 64, 3, 4, 2, false, true, BWD_ROWS, 1, true>(p, stream)
                 : launch_bwd<256, 128, 64, 3, 4, 2, false, true, BWD_ROWS, 1, false>(p, stream);
-    return kt ? launch_bwd<256, 256, 64, 2, 2, 4, false, true, BWD_ROWS, 1, true>(p, stream)
-              : launch_bwd<256, 256, 64, 2, 2, 4, false, true, BWD_ROWS, 1, false>(p, stream);
+    return launch_phase_bwd(256, p, stream);
   }
   if (p.mode == BWD_KSEG) {
     // weight gradients: both operands row-major activations reduced over the group's rows
     if (!p.x_mn || !p.w_mn || p.M < 8 || p.M % 8) return hipErrorInvalidValue;
-    // 256 x 256 tiles, two 64-wide slices in flight: measured against 128 x 128 tiles with two
-    // or three workgroups per CU and three 32-wide slices in flight (routed dW13 at DeepSeek-V3
-    // 1079-1132 us against 985)
+    // 256 x 256 tiles of the phase kernel
     // the router's weight gradient (float32 K-split partials, M = the expert count): 128 x 128
     // tiles, two workgroups per CU, 4x the tiles of 256 x 256 ones for its few output tiles
     // (DeepSeek-V3: 256 x 7168 outputs over 9 token chunks, 76 -> 59 us)
     if (p.Yf) return launch_bwd<128, 128, 64, 2, 2, 2, true, true, BWD_KSEG, 2>(p, stream);
-#ifdef MOE_BWD_KSEG_CFG
-    // tuning alternatives (not chosen by the launcher)
-    switch (MOE_BWD_KSEG_CFG) {
-      case 1: return launch_bwd<128, 128, 64, 2, 2, 2, true, true, BWD_KSEG, 2>(p, stream);
-      case 3: return launch_bwd<128, 128, 32, 4, 2, 2, true, true, BWD_KSEG, 2>(p, stream);
-      case 4: return launch_bwd<128, 128, 32, 3, 2, 2, true, true, BWD_KSEG, 3>(p, stream);
-      default: break;
-    }
-#endif
-    return launch_bwd<256, 256, 64, 2, 4, 2, true, true, BWD_KSEG, 1>(p, stream);
+    return launch_phase_bwd(256, p, stream);
   }
   return hipErrorInvalidValue;
 }

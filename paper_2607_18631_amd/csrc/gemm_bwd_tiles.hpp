@@ -1,0 +1,98 @@
+// Tiles of the backward GEMMs (gemm_bwd.hip, gemm_phase_bwd.hip): the segment table and its decoding.
+#pragma once
+#include "common.hpp"
+#include "gemm_device.hpp"
+#include "kernels.hpp"
+
+namespace moe {
+
+// The phase kernel on bm x 256 tiles: row segments (bm = 256 or 320) and K segments with bf16
+// results (bm = 256).  gemm_phase_bwd.hip.
+hipError_t launch_phase_bwd(int bm, const GemmBwdProblem& p, hipStream_t stream);
+
+// One tile: output rows [m0, m_end) x columns [n0, N) of group g, K range [kbeg, kbeg + klen).
+struct BTile {
+  int g, m0, m_end, n0, kbeg, klen;
+};
+
+// Segment table in LDS: begin s_off / length s_len of every group (clamped to the row bound) and, for
+// row segments, the first tile s_tp of each; tn output tiles per m-tile.  Returns the launch's tile
+// count.  Every thread of the block calls this.
+template <int MODE, int NTH, int BM>
+__device__ __forceinline__ int bwd_tile_table(const GemmBwdProblem& p, int tn, int* s_off, int* s_len, int* s_tp,
+                                              int* s_tmp) {
+  const int tid = threadIdx.x, groups = p.groups;
+  const int cap = (int)p.max_rows;
+  for (int g = tid; g < groups; g += NTH) {
+    int b, e;
+    if (p.seg_stride > 0) {
+      b = g * p.seg_stride;
+      e = b + min(max(p.offsets[g], 0), p.seg_stride);
+    } else {
+      b = min(max(p.offsets[g], 0), cap);
+      e = min(max(p.offsets[g + 1], b), cap);
+    }
+    s_off[g] = b;
+    s_len[g] = e - b;
+  }
+  __syncthreads();
+  if constexpr (MODE == BWD_KSEG) return groups * ((p.M + BM - 1) / BM) * tn;
+  // tiles per group = ceil(len / BM) * tn, prefix-summed into s_tp (first tile of g)
+  constexpr int PER = (kMaxGroups + NTH - 1) / NTH;
+  int loc[PER], lsum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int g = tid * PER + i;
+    loc[i] = g < groups ? ((s_len[g] + BM - 1) / BM) * tn : 0;
+    lsum += loc[i];
+  }
+  int excl;
+  const int total = block_exclusive_scan<NTH>(lsum, s_tmp, excl);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int g = tid * PER + i;
+    if (g < groups) s_tp[g] = excl;
+    excl += loc[i];
+  }
+  if (tid == 0) s_tp[groups] = total;
+  __syncthreads();
+  return total;
+}
+
+template <int MODE, int BM, int BN>
+__device__ __forceinline__ BTile bwd_decode(const GemmBwdProblem& p, int tile, int tn, const int* s_off,
+                                            const int* s_len, const int* s_tp) {
+  BTile t;
+  if constexpr (MODE == BWD_ROWS) {
+    int lo = 0, hi = p.groups;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (s_tp[mid] <= tile) lo = mid; else hi = mid;
+    }
+    t.g = __builtin_amdgcn_readfirstlane(lo);
+    const int local = tile - __builtin_amdgcn_readfirstlane(s_tp[t.g]);
+    const int len = __builtin_amdgcn_readfirstlane(s_len[t.g]);
+    const int tm = (len + BM - 1) / BM;
+    const int mi = local % tm, ni = local / tm;           // m-fastest: tiles of one weight panel adjacent
+    const int b = __builtin_amdgcn_readfirstlane(s_off[t.g]);
+    t.m0 = b + mi * BM;
+    t.m_end = b + len;
+    t.n0 = ni * BN;
+    t.kbeg = 0;
+    t.klen = p.K;
+  } else {
+    const int tm = (p.M + BM - 1) / BM;
+    t.g = tile / (tm * tn);
+    const int local = tile - t.g * tm * tn;
+    // n-fastest: the tiles an XCD runs together store whole output rows (32 experts of 255 rows, d = 7168,
+    // F = 2048: dW13 785 us m-fastest, 739 in blocks of 4 x 8 tiles, 720 n-fastest)
+    t.m0 = (local / tn) * BM;
+    t.m_end = p.M;
+    t.n0 = (local % tn) * BN;
+    t.kbeg = __builtin_amdgcn_readfirstlane(s_off[t.g]);
+    t.klen = __builtin_amdgcn_readfirstlane(s_len[t.g]);
+  }
+  return t;
+}
+
+}  // namespace moe

@@ -11,7 +11,21 @@ namespace moe {
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"I"(N) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// vmcnt(HI) if x == 0 (wave-uniform), else vmcnt(LO), HI >= LO.  The branch stays inside the asm: a branch
+// the compiler sees between two MFMA sequences costs it the accumulators' registers.
+template <int HI, int LO>
+__device__ __forceinline__ void wait_vmcnt_sel(int x) {
+  static_assert(HI >= LO && LO >= 0 && HI < 64, "vmcnt range");
+  if constexpr (HI == LO) {
+    wait_vmcnt<LO>();
+  } else {
+    asm volatile("s_waitcnt vmcnt(%1)\n\ts_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 .Lwait%=\n\ts_waitcnt vmcnt(%2)\n.Lwait%=:" ::"s"(
+                     __builtin_amdgcn_readfirstlane(x)),
+                 "n"(HI), "n"(LO)
+                 : "memory", "scc");
+  }
 }
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void raw_barrier() { asm volatile("s_barrier" ::: "memory"); }
@@ -37,12 +51,22 @@ __device__ __forceinline__ void dma16_sv(const char* sbase, uint32_t voff, bf16_
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
                : "memory", "m0");
 }
+// The same where `on` is set (wave-uniform; the branch inside the asm, as in wait_vmcnt_sel).
+__device__ __forceinline__ void dma16_sv_if(int on, const char* sbase, uint32_t voff, bf16_t* dst) {
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(dst);
+  asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lcopy%=\n\ts_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n.Lcopy%=:" ::"v"(voff),
+               "s"(sbase), "s"(lds), "s"(__builtin_amdgcn_readfirstlane(on))
+               : "memory", "m0", "scc");
+}
 // The same from a 64-bit address of the lane's own.
 __device__ __forceinline__ void dma16_v(const char* src, bf16_t* dst) {
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(dst);
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory", "m0");
 }
 #pragma clang diagnostic pop
+
+// 16 zero bytes: what a lane copies for a chunk past K
+static __device__ __align__(16) const uint32_t g_zero_chunk[4] = {0, 0, 0, 0};
 
 template <int BK>
 struct Swz {

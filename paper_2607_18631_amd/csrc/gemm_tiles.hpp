@@ -18,10 +18,9 @@ hipError_t launch_phase_gemm(int bm, const GemmProblem& p, hipStream_t stream);
 // epilogues whose weight tile pairs gate rows [0, N) with up rows [N, 2N)
 constexpr bool swiglu_pairs(int epi) { return epi == EPI_SWIGLU || epi == EPI_SWIGLU_BWD; }
 
-#ifndef MOE_BAND_M
-#define MOE_BAND_M 8
-#endif
-constexpr int BAND_M = MOE_BAND_M;   // m-tiles per band of the tile order
+// m-tiles per band of the tile order: 4 against 8 measured 2% faster on the up-projection of 4096 tokens x 8
+// experts of 14336 (1450 -> 1421 us), within noise elsewhere
+constexpr int BAND_M = 4;
 
 // ---------------------------------------------------------------------------------------
 // Tile table, tile decoding, slice copies, epilogue
@@ -230,9 +229,6 @@ __device__ __forceinline__ int round_position(int r, int slot) {
   return r * G + ((r & 1) ? G - 1 - slot : slot);
 }
 
-// 16 zero bytes: what a lane copies for a chunk past K
-static __device__ __align__(16) const uint32_t g_zero_chunk[4] = {0, 0, 0, 0};
-
 // Copies of one K slice of a tile into a ring slot, spread over NW waves.  Per tile, a
 // wave-uniform base (scalar registers) per copy instruction and a fixed per-lane 32-bit byte
 // offset (row * ld + logical chunk), so a full slice's copies cost one scalar add each and
@@ -329,11 +325,11 @@ struct CopyPlan {
     }
   }
 
-  // Copy J of K slice kt for the phase-pipelined kernel.  KT: K is no multiple of BK, and the
-  // lanes whose chunk lies past K fetch 16 zero bytes instead (both operands), so the partial last
-  // slice needs no clean-up in LDS.
+  // Copy J of K slice kt for the phase loop.  KT: slice kt is the last and K is no multiple of BK; the
+  // lanes whose chunk lies past K fetch 16 zero bytes instead (both operands), so the partial slice
+  // needs no clean-up in LDS.
   template <bool KT, int J>
-  __device__ __forceinline__ void issue_pipe_one(bf16_t* dst, int kt, int wave, int K) const {
+  __device__ __forceinline__ void issue_block(bf16_t* dst, int kt, int wave, int K) const {
     if constexpr (!KT) {
       issue_one_sv<J>(dst, kt, wave);
     } else {
@@ -346,22 +342,6 @@ struct CopyPlan {
       dma16_v(src, dst + (J < LX ? (wave + NW * J) * 512 : BM * BK + (wave + NW * (J - LX)) * 512));
     }
   }
-  // token blocks J < ph / all weight rows of slice kt
-  template <bool KT, int J, int END>
-  __device__ __forceinline__ void issue_pipe(bf16_t* dst, int kt, int wave, int K, int ph) const {
-    if constexpr (J < END) {
-      if (J < ph) issue_pipe_one<KT, J>(dst, kt, wave, K);
-      issue_pipe<KT, J + 1, END>(dst, kt, wave, K, ph);
-    }
-  }
-  template <bool KT, int J>
-  __device__ __forceinline__ void issue_pipe_w(bf16_t* dst, int kt, int wave, int K) const {
-    if constexpr (J < LW) {
-      issue_pipe_one<KT, LX + J>(dst, kt, wave, K);
-      issue_pipe_w<KT, J + 1>(dst, kt, wave, K);
-    }
-  }
-
   // the partial last slice (K % BK != 0): chunks past K are fetched from K-8 and zeroed later
   __device__ __forceinline__ void issue_tail(bf16_t* dst, int kt, int wave, int K) const {
     const int k0 = kt * BK;

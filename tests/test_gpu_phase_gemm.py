@@ -10,6 +10,7 @@ import pytest
 import torch
 
 import oracle
+from oracle import moe_backward as obwd
 from paper_2607_18631_amd import moe
 from paper_2607_18631_amd import workloads as wl
 
@@ -44,3 +45,38 @@ def test_segment_ends_and_slice_counts(rows_hint, F, d):
         if a < b:
             ref = oracle.swiglu_ffn(oracle.bf16_to_f64(x[a:b]), oracle.bf16_to_f64(w13[e]), oracle.bf16_to_f64(w2[e]))
             assert rel_fro(got[a:b], ref) <= REL_TOL, (e, COUNTS[e])
+
+
+def test_backward_slice_counts_between_tiles():
+    """moe_grouped_ffn_backward on 48 segments of none to seven 64-row slices in turn, with more weight-gradient
+    tiles than workgroups: a tile's last slices issue the next tile's first ones when both have three or
+    more, and every change between such tiles, shorter ones and empty ones follows another.  Output
+    edges cut tiles in both directions, and the row products' reductions end in a partial slice.  Each
+    gradient within rel. Frobenius 5e-3 (bf16 results of at most two bf16 intermediates)."""
+    counts = [0, 5, 193, 250, 64, 256, 65, 300, 128, 129, 192, 420] * 4
+    E, d, F = len(counts), 1000, 504
+    sh = wl.MoEShape(T=200 * E, d=d, E=E, top_k=1, F=F, E_local=E)
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    n = int(offs[-1])
+    rng = np.random.default_rng(3)
+    draw = lambda shape, std: wl.f32_to_bf16_bits((rng.standard_normal(shape, dtype=np.float32) * np.float32(std)))
+    x, dy = draw((n, d), 1.0), draw((n, d), 1.0)
+    w13, w2 = draw((E, 2 * F, d), d ** -0.5), draw((E, d, F), F ** -0.5)
+    rows = lambda b: torch.cat([moe.to_device_bf16(b), torch.zeros(sh.capacity - n, d, dtype=torch.bfloat16, device="cuda")])
+    nan = lambda *s: torch.full(s, float("nan"), dtype=torch.bfloat16, device="cuda")
+    dx, dw13, dw2 = nan(sh.capacity, d), nan(E, 2 * F, d), nan(E, d, F)
+    print("[phase gemm] backward", flush=True)
+    moe.moe_grouped_ffn_backward(sh, rows(x), torch.from_numpy(offs).cuda(), moe.to_device_bf16(w13),
+                                 moe.to_device_bf16(w2), rows(dy), dx, dw13, dw2,
+                                 moe.alloc_workspace(sh, moe.MOE_WS_FFN_BWD))
+    torch.cuda.synchronize()
+    f64 = lambda t: oracle.bf16_to_f64(dev_bits(t))
+    for e in range(E):
+        a, b = offs[e], offs[e + 1]
+        if a == b:
+            assert not f64(dw13[e]).any() and not f64(dw2[e]).any(), e
+            continue
+        ref = obwd.swiglu_ffn_backward(oracle.bf16_to_f64(x[a:b]), oracle.bf16_to_f64(w13[e]),
+                                       oracle.bf16_to_f64(w2[e]), oracle.bf16_to_f64(dy[a:b]))
+        for name, got, want in zip(("dx", "dw13", "dw2"), (dx[a:b], dw13[e], dw2[e]), ref):
+            assert rel_fro(f64(got), want) <= REL_TOL, (name, e, counts[e])
