@@ -675,9 +675,9 @@ hipError_t launch_grouped_gemm(const GemmProblem& p, hipStream_t stream) {
   // equal-stride segments must fit the row bound
   if (p.seg_stride > 0 && (p.offsets == nullptr || (int64_t)p.groups * p.seg_stride > p.max_rows))
     return hipErrorInvalidValue;
-  // 256 x 256 tiles, 8 waves, two 64-wide K slices in flight: the best measured on the DeepSeek-V3,
-  // Mixtral and skewed workloads (largest reuse per byte copied into LDS; also whenever a large
-  // dense extra group shares the launch).  With few expected rows per group the launch is a
+  // 256 x 256 tiles of the phase kernel: the best measured on the DeepSeek-V3, Mixtral and skewed
+  // workloads (largest reuse per byte copied into LDS; also whenever a large dense extra group shares
+  // the launch).  With few expected rows per group the launch is a
   // weight stream over few m-tiles, spread over more workgroups by smaller tiles: 64 x 128 up to
   // 128 rows per group (1.4-1.8x faster at 2-128 rows), 128 x 256 up to 512 (1.1-1.5x).
   const bool small_extra = p.rows2 <= 512;
@@ -731,6 +731,13 @@ hipError_t launch_grouped_gemm(const GemmProblem& p, hipStream_t stream) {
       const double c6 = rounds(m256 * tn256), c7 = 0.6 * rounds(m256 * tn);
       if (c8 < c6 && c8 <= c7) cfg_bf16 = 8;
       else if (c7 < c6) cfg_bf16 = 7;
+    }
+    // A launch whose 256-row tiles cover at most a quarter of the chip takes 64 x 128 ones, an eighth of
+    // the work each and two workgroups per CU, so they still fit about one round.  3001 rows x a
+    // shared expert of F = 264, d = 2040: up-projection 36 tiles of 256 x 256 109 us, 235 of 64 x 128 26 us.
+    if (tier == 6 && p.rows2 == 0) {
+      if (m256 * tn <= cus / 4) cfg_swiglu = cfg_swiglu_bwd = 20;
+      if (m256 * tn256 <= cus / 4) cfg_bf16 = 20;
     }
     // On 320-row tiles, a dense extra group (the shared expert) is tiled 256 rows high when that
     // adds no round: its tiles then carry the 8 live token blocks the routed ones do (the routed

@@ -18,7 +18,7 @@ from parity_util import REL_TOL, dev_bits, rel_fro
 
 pytestmark = pytest.mark.gpu
 
-COUNTS = [0, 1, 31, 32, 33, 64, 65, 97, 129, 160, 191, 225, 255, 256, 257, 319, 321]
+COUNTS = [0, 1, 31, 32, 33, 64, 65, 97, 129, 160, 191, 225, 255, 256, 257, 319, 321] * 2
 
 
 @pytest.mark.parametrize("rows_hint, F", [(600, 136), (700, 640)], ids=["tile256", "tile320"])
@@ -45,6 +45,28 @@ def test_segment_ends_and_slice_counts(rows_hint, F, d):
         if a < b:
             ref = oracle.swiglu_ffn(oracle.bf16_to_f64(x[a:b]), oracle.bf16_to_f64(w13[e]), oracle.bf16_to_f64(w2[e]))
             assert rel_fro(got[a:b], ref) <= REL_TOL, (e, COUNTS[e])
+
+
+@pytest.mark.parametrize("T, d, F", [(3001, 200, 264), (513, 64, 8), (1000, 1032, 40)])
+def test_few_large_tiles_take_small_ones(T, d, F):
+    """One dense segment whose 256-row tiles would cover at most a quarter of the chip runs on 64-row tiles:
+    the same results, bit for bit, as the rows in groups of at most 128 (the small tiles of such groups)."""
+    rng = np.random.default_rng(T)
+    draw = lambda shape, std: moe.to_device_bf16(wl.f32_to_bf16_bits((rng.standard_normal(shape) * std).astype(np.float32)))
+    x, w13, w2 = draw((T, d), 1.0), draw((1, 2 * F, d), d ** -0.5), draw((1, d, F), F ** -0.5)
+    outs = []
+    for E in (1, -(-T // 100)):
+        sh = wl.MoEShape(T=T, d=d, E=E, top_k=1, F=F, E_local=E)
+        offs = np.minimum(np.arange(E + 1) * (T if E == 1 else 100), T).astype(np.int32)
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        print(f"[phase gemm] small launch T {T} d {d} F {F} groups {E}", flush=True)
+        moe.moe_grouped_ffn(sh, x, torch.from_numpy(offs).cuda(), w13.expand(E, -1, -1).contiguous(),
+                            w2.expand(E, -1, -1).contiguous(), y, moe.alloc_workspace(sh, moe.MOE_WS_FFN))
+        torch.cuda.synchronize()
+        outs.append(dev_bits(y))
+    ref = oracle.swiglu_ffn(*(oracle.bf16_to_f64(dev_bits(t)) for t in (x, w13[0], w2[0])))
+    assert rel_fro(oracle.bf16_to_f64(outs[0]), ref) <= REL_TOL
+    assert np.array_equal(outs[0], outs[1])
 
 
 def test_backward_slice_counts_between_tiles():
