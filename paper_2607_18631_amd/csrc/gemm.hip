@@ -723,8 +723,9 @@ hipError_t launch_grouped_gemm(const GemmProblem& p, hipStream_t stream) {
     // SwiGLU epilogues: a 256-row weight tile yields 128 output columns
     const double s_base = tier == 5 ? 0.7 * rounds(m128 * tn) : rounds(m256 * tn);
     if (1.15 * rounds(m320 * tn) < s_base) cfg_swiglu = cfg_swiglu_bwd = 8;
-    // bf16 epilogue: also 256 x 128 tiles on the 256-row tier
-    const double c8 = 1.15 * rounds(m320 * tn256);
+    // bf16 epilogue: also 256 x 128 tiles on the 256-row tier; no 320-row tiles with a K tail (that instance
+    // reloads spilled registers next to its K loops, whose waits then cover every copy in flight)
+    const double c8 = p.K % 64 ? 1e30 : 1.15 * rounds(m320 * tn256);
     if (tier == 5) {
       if (c8 < 0.7 * rounds(m128 * tn256)) cfg_bf16 = 8;
     } else {
