@@ -38,6 +38,7 @@
 #include "common.hpp"
 #include "gemm_bwd_tiles.hpp"
 #include "gemm_device.hpp"
+#include "gemm_phase_bwd.hpp"
 #include "kernels.hpp"
 
 namespace moe {
@@ -465,7 +466,7 @@ hipError_t launch_gemm_bwd(const GemmBwdProblem& p, hipStream_t stream) {
     auto rounds = [&](double tiles) { return std::max(1.0, std::ceil(tiles / cus - 0.05)); };
     const double tn256 = (double)((p.N + 255) / 256), tn128 = (double)((p.N + 127) / 128);
     const double c1 = rounds(mtiles(256) * tn256), c2 = 0.6 * rounds(mtiles(256) * tn128);
-    const double c3 = 1.15 * rounds(mtiles(320) * tn256);
+    const double c3 = kt ? 1e30 : 1.15 * rounds(mtiles(320) * tn256);   // no tail instance of it
     const int cfg = (c3 < c1 && c3 <= c2) ? 3 : c2 < c1 ? 2 : 1;
     if (cfg == 3) return launch_phase_bwd(320, p, stream);
     if (cfg == 2)

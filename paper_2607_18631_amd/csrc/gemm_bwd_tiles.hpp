@@ -1,4 +1,4 @@
-// Tiles of the backward GEMMs (gemm_bwd.hip, gemm_phase_bwd.hip): the segment table and its decoding.
+// Tiles of the backward GEMMs (gemm_bwd.hip, gemm_phase_bwd.hpp): the segment table and its decoding.
 #pragma once
 #include "common.hpp"
 #include "gemm_device.hpp"
@@ -7,7 +7,7 @@
 namespace moe {
 
 // The phase kernel on bm x 256 tiles: row segments (bm = 256 or 320) and K segments with bf16
-// results (bm = 256).  gemm_phase_bwd.hip.
+// results (bm = 256).  gemm_phase_bwd.hpp.
 hipError_t launch_phase_bwd(int bm, const GemmBwdProblem& p, hipStream_t stream);
 
 // One tile: output rows [m0, m_end) x columns [n0, N) of group g, K range [kbeg, kbeg + klen).

@@ -2,7 +2,7 @@
 //   row segments (dA, dX, the router's dx): K-major token rows against an MN-major weight;
 //   K segments (per-expert weight gradients): both operands MN-major, one M x N output per group,
 //   reduced over the group's rows.
-// See gemm_bwd.hip for the problem and the smaller tiles.
+// Part of gemm_bwd.hip, which has the problem and the smaller tiles.
 //
 // What bounds them, and what was measured (8192 tokens, d = 7168, 32 experts and a shared one of F = 2048;
 // before: 32 x 32 x 16 MFMAs, one slice of copy lead, results staged in LDS):
@@ -13,6 +13,7 @@
 //    over the stores still in flight; without any store the launch takes 516 us, and the stores, 1.9 GB at
 //    about 7 TB/s, come on top: loads wait behind stores in the same in-order counter.
 //  - shared dW13 463 -> 417, dW2 218 -> 209 (K = 8192).
+#pragma once
 #include <type_traits>
 
 #include "common.hpp"
@@ -261,7 +262,8 @@ hipError_t launch_phase_bwd(int bm, const GemmBwdProblem& p, hipStream_t stream)
   }
   const bool kt = p.K % 64 != 0;
   if (bm == 256) return kt ? launch<256, BWD_ROWS, true>(p, stream) : launch<256, BWD_ROWS, false>(p, stream);
-  if (bm == 320) return kt ? launch<320, BWD_ROWS, true>(p, stream) : launch<320, BWD_ROWS, false>(p, stream);
+  // 320 rows with K-tail code would reload spilled registers inside its K loop
+  if (bm == 320 && !kt) return launch<320, BWD_ROWS, false>(p, stream);
   return hipErrorInvalidValue;
 }
 

@@ -1,4 +1,4 @@
-// The phase-pipelined K loop of the large-tile GEMMs (gemm_phase.hip, gemm_phase_bwd.hip): a BM x 256
+// The phase-pipelined K loop of the large-tile GEMMs (gemm_phase.hip, gemm_phase_bwd.hpp): a BM x 256
 // tile (BM = 256 or 320) of 8 waves, 2 (token rows) x 4 (weight rows), each 32 rows of every 64-row token
 // block x 64 weight rows, on v_mfma_f32_16x16x32_bf16.
 #pragma once
