@@ -43,25 +43,28 @@ __device__ __forceinline__ void dma16(const bf16_t* src, bf16_t* dst) {
 // knows of (vmcnt(0)), which would serialise each slice's copies with the next slice's MFMAs.
 // Copies issued this way are invisible to it; the kernel orders them itself (explicit vmcnt
 // counts and barriers).  M0 carries the LDS address; the asm declares M0 clobbered, so the
-// compiler keeps nothing of its own there across it.
+// compiler keeps nothing of its own there across it.  A scalar write of M0 and a direct-to-LDS
+// load that takes its address there need one wait state between them, which the hardware does
+// not insert and the compiler cannot add inside an asm string: the s_nop (or the compare and
+// branch of dma16_sv_if).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void dma16_sv(const char* sbase, uint32_t voff, bf16_t* dst) {
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(dst);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
                : "memory", "m0");
 }
 // The same where `on` is set (wave-uniform; the branch inside the asm, as in wait_vmcnt_sel).
 __device__ __forceinline__ void dma16_sv_if(int on, const char* sbase, uint32_t voff, bf16_t* dst) {
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(dst);
-  asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lcopy%=\n\ts_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n.Lcopy%=:" ::"v"(voff),
+  asm volatile("s_mov_b32 m0, %2\n\ts_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lcopy%=\n\tglobal_load_lds_dwordx4 %0, %1\n.Lcopy%=:" ::"v"(voff),
                "s"(sbase), "s"(lds), "s"(__builtin_amdgcn_readfirstlane(on))
                : "memory", "m0", "scc");
 }
 // The same from a 64-bit address of the lane's own.
 __device__ __forceinline__ void dma16_v(const char* src, bf16_t* dst) {
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(dst);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 

@@ -5,7 +5,10 @@ to scratch.  Those accesses must stay outside the K loops: inside, a scratch loa
 memory load like the slice copies, and waiting for it (vmcnt counts in issue order) would also
 wait for every copy in flight.  For every kernel with MFMAs this test finds its innermost loops
 that contain MFMAs (a backward branch to an earlier label) and checks that no scratch access sits
-inside one."""
+inside one.
+
+The slice copies written as inline assembly keep the wait state between a scalar write of M0 (their
+LDS address) and the direct-to-LDS load that reads it, which the compiler does not see."""
 import os
 import re
 import shutil
@@ -49,7 +52,7 @@ def _mfma_loops(lines):
 @pytest.fixture(scope="module")
 def device_asm(tmp_path_factory):
     d = tmp_path_factory.mktemp("asm")
-    srcs = ["gemm.hip", "gemm_bwd.hip"]
+    srcs = ["gemm.hip", "gemm_phase.hip", "gemm_bwd.hip"]
     with ThreadPoolExecutor(len(srcs)) as ex:
         texts = list(ex.map(lambda s: _device_asm(s, str(d / (s + ".s"))), srcs))
     return dict(zip(srcs, texts))
@@ -71,6 +74,37 @@ def test_no_scratch_in_mfma_loops(device_asm, src):
         checked += 1
     assert checked >= 8, f"only {checked} MFMA kernels found in {src}"
     print(f"[codegen] {src}: {checked} MFMA kernels, no scratch access inside their K loops")
+
+
+def _m0_hazards(lines):
+    """Direct-to-LDS loads whose very next preceding instruction writes M0 by a scalar instruction."""
+    found, prev = [], ""
+    for l in lines:
+        ins = l.split(";")[0].strip()
+        if not ins or ins.endswith(":") or ins.startswith("."):
+            continue
+        if re.match(r"(global|buffer|scratch)_load_lds|buffer_load_\w+ .*\blds\b", ins) and re.match(r"s_\w+\s+m0\b", prev):
+            found.append((prev, ins))
+        prev = ins
+    return found
+
+
+@pytest.mark.parametrize("src", ["gemm.hip", "gemm_phase.hip", "gemm_bwd.hip"])
+def test_lds_copies_wait_for_m0(device_asm, src):
+    lines = device_asm[src].split("\n")
+    copies = sum("global_load_lds" in l for l in lines)
+    assert copies >= 100, f"only {copies} slice copies found in {src}"
+    bad = _m0_hazards(lines)
+    assert not bad, f"{len(bad)} of {copies} copies directly behind a write of M0: {bad[:2]}"
+
+
+def test_m0_finder():
+    """On hand-written listings: a copy right behind a write of M0 (assembler comments and a label
+    between) is found; one with a wait state, another instruction or another register is not."""
+    bad = "\ts_mov_b32 m0, s1\n\t;;#x\n.Lcopy0:\n\tglobal_load_lds_dwordx4 v1, s[2:3]"
+    assert len(_m0_hazards(bad.split("\n"))) == 1
+    for mid in ("\ts_nop 0\n", "\ts_cmp_eq_u32 s4, 0\n", "\ts_mov_b32 s5, s6\n"):
+        assert not _m0_hazards(("\ts_mov_b32 m0, s1\n" + mid + "\tglobal_load_lds_dwordx4 v1, s[2:3]").split("\n"))
 
 
 def test_loop_finder_sees_scratch_in_a_loop():
