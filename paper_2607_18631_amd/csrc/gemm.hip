@@ -48,14 +48,13 @@
 //
 // This file holds the ring kernel (tiles of 64 x 64 to 256 x 128) and the choice of tiles; the
 // 256 x 256 and 320 x 256 tiles run in gemm_phase.hip.
-#include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
 #include "gemm_device.hpp"
 #include "gemm_tiles.hpp"
 #include "kernels.hpp"
+#include "tile_rule.hpp"
 
 namespace moe {
 
@@ -652,19 +651,19 @@ hipError_t launch_tile(const GemmProblem& p, hipStream_t stream) {
 }
 
 template <int EPI>
-hipError_t launch_cfg(int cfg, const GemmProblem& p, hipStream_t stream) {
-  switch (cfg) {
-    case 5: return launch_tile<128, 256, 64, 3, 2, 4, EPI>(p, stream);
-    case 6: return launch_phase_gemm(256, p, stream);
-    case 7: return launch_tile<256, 128, 64, 3, 4, 2, EPI>(p, stream);
-    case 8: return launch_phase_gemm(320, p, stream);
+hipError_t launch_cfg(Tile tile, const GemmProblem& p, hipStream_t stream) {
+  switch (tile) {
+    case TILE_128X256: return launch_tile<128, 256, 64, 3, 2, 4, EPI>(p, stream);
+    case TILE_256X128:
+      if constexpr (EPI == EPI_BF16) return launch_tile<256, 128, 64, 3, 4, 2, EPI>(p, stream);
+      break;
+    case TILE_256X256: return launch_phase_gemm(256, p, stream);
+    case TILE_320X256: return launch_phase_gemm(320, p, stream);
     // few rows per group (decode-like): 64 x 128 tiles, 4 waves, 3-slot ring, two workgroups per CU
-    case 20: return launch_tile<64, 128, 64, 3, 2, 2, EPI>(p, stream);
-    default: break;
+    case TILE_64X128: return launch_tile<64, 128, 64, 3, 2, 2, EPI>(p, stream);
   }
   return hipErrorInvalidValue;
 }
-
 
 }  // namespace
 
@@ -675,103 +674,23 @@ hipError_t launch_grouped_gemm(const GemmProblem& p, hipStream_t stream) {
   // equal-stride segments must fit the row bound
   if (p.seg_stride > 0 && (p.offsets == nullptr || (int64_t)p.groups * p.seg_stride > p.max_rows))
     return hipErrorInvalidValue;
-  // 256 x 256 tiles of the phase kernel: the best measured on the DeepSeek-V3, Mixtral and skewed
-  // workloads (largest reuse per byte copied into LDS; also whenever a large dense extra group shares
-  // the launch).  With few expected rows per group the launch is a
-  // weight stream over few m-tiles, spread over more workgroups by smaller tiles: 64 x 128 up to
-  // 128 rows per group (1.4-1.8x faster at 2-128 rows), 128 x 256 up to 512 (1.1-1.5x).
-  const bool small_extra = p.rows2 <= 512;
-  const int tier = (p.rows_hint > 0 && small_extra) ? (p.rows_hint <= 128 ? 20 : p.rows_hint <= 512 ? 5 : 6) : 6;
-  int cfg_swiglu = tier, cfg_bf16 = tier;
-  // Tile shape from the expected tile count of each shape.  A persistent launch takes about
-  // ceil(tiles / CUs) rounds of its slowest workgroup; per tile, a 320 x 256 tile (10 token
-  // blocks, 2 x 4 waves) costs ~1.15 of a 256 x 256 one, a 128 x 256 tile ~0.7, a 256 x 128 tile
-  // ~0.6 (measured).  The per-expert row counts of a routed batch scatter around their mean
-  // (standard deviation about its square root), so an expert whose mean is 256 rows takes 1.5
-  // 256-row m-tiles on average but one 320-row tile: DeepSeek-V3 shapes (256 rows per expert,
-  // shared expert of 8192 rows in the launch) run both projections on 320-row tiles (up
-  // 1085-1093 -> 1000-1025 us, down 588-596 -> 565-568), Mixtral shapes (1024 rows per expert,
-  // 2.25 rounds of 256 x 256 down-projection tiles) their down-projection (1137-1147 -> 944-955;
-  // 256 x 128 tiles: 1097), while Mixtral's up-projection (15.75 rounds either way) and the
-  // skewed workload stay on 256 x 256.  The backward's recomputed up-projection of the routed
-  // experts alone (tier 128 x 256) takes 320-row tiles at DeepSeek-V3 (627 -> 521 us).
-  int cfg_swiglu_bwd = tier;
-  int rows2_tile = 0;
-  if ((tier == 5 || tier == 6) && p.rows_hint > 0) {
-    const double cus = cu_count();
-    const int64_t groups = p.offsets ? p.groups : 1;
-    const double mu = (double)p.rows_hint;
-    const double sigma = groups > 1 ? std::sqrt(mu) : 0.0;
-    auto grouped_mtiles = [&](int bm) {                  // expected m-tiles of the groups
-      double per_group = 0;
-      if (sigma == 0) {
-        per_group = std::ceil(mu / bm);
-      } else {
-        const int jmax = (int)((mu + 8 * sigma) / bm) + 1;
-        for (int j = 0; j <= jmax; ++j)                   // E[ceil(m / bm)] = sum_j P(m > j bm)
-          per_group += 0.5 * std::erfc((j * bm - mu) / (sigma * std::sqrt(2.0)));
-      }
-      return per_group * groups;
-    };
-    auto mtiles = [&](int bm) { return grouped_mtiles(bm) + std::ceil((double)p.rows2 / bm); };
-    // rounds of the persistent grid; an expected count a few hundredths of a round above a
-    // whole number (the normal tail of the row counts) is that whole number
-    auto rounds = [&](double tiles) { return std::max(1.0, std::ceil(tiles / cus - 0.05)); };
-    const double tn = (double)((p.N + 127) / 128);        // 128-column output blocks
-    const double tn256 = std::ceil(tn / 2);
-    const double m128 = mtiles(128), m256 = mtiles(256), m320 = mtiles(320);
-    // SwiGLU epilogues: a 256-row weight tile yields 128 output columns
-    const double s_base = tier == 5 ? 0.7 * rounds(m128 * tn) : rounds(m256 * tn);
-    if (1.15 * rounds(m320 * tn) < s_base) cfg_swiglu = cfg_swiglu_bwd = 8;
-    // bf16 epilogue: also 256 x 128 tiles on the 256-row tier; no 320-row tiles with a K tail (that instance
-    // reloads spilled registers next to its K loops, whose waits then cover every copy in flight)
-    const double c8 = p.K % 64 ? 1e30 : 1.15 * rounds(m320 * tn256);
-    if (tier == 5) {
-      if (c8 < 0.7 * rounds(m128 * tn256)) cfg_bf16 = 8;
-    } else {
-      const double c6 = rounds(m256 * tn256), c7 = 0.6 * rounds(m256 * tn);
-      if (c8 < c6 && c8 <= c7) cfg_bf16 = 8;
-      else if (c7 < c6) cfg_bf16 = 7;
-    }
-    // A launch whose 256-row tiles cover at most a quarter of the chip takes 64 x 128 ones, an eighth of
-    // the work each and two workgroups per CU, so they still fit about one round.  3001 rows x a
-    // shared expert of F = 264, d = 2040: up-projection 36 tiles of 256 x 256 109 us, 235 of 64 x 128 26 us.
-    if (tier == 6 && p.rows2 == 0) {
-      if (m256 * tn <= cus / 4) cfg_swiglu = cfg_swiglu_bwd = 20;
-      if (m256 * tn256 <= cus / 4) cfg_bf16 = 20;
-    }
-    // On 320-row tiles, a dense extra group (the shared expert) is tiled 256 rows high when that
-    // adds no round: its tiles then carry the 8 live token blocks the routed ones do (the routed
-    // experts' ~256 rows), instead of 10.  DeepSeek-V3 shapes: up-projection 928 -> 1024 tiles
-    // (4 rounds either way), down-projection 1624 -> 1792 (7 rounds either way).
-    const int my_cfg = p.epi == EPI_SWIGLU ? cfg_swiglu : p.epi == EPI_BF16 ? cfg_bf16 : 0;
-    if (my_cfg == 8 && p.rows2 > 256) {
-      const double cols = p.epi == EPI_SWIGLU ? tn : tn256;
-      const double g320 = grouped_mtiles(320);
-      if (rounds((g320 + std::ceil(p.rows2 / 256.0)) * cols) <= rounds((g320 + std::ceil(p.rows2 / 320.0)) * cols))
-        rows2_tile = 256;
-    }
-  }
   GemmProblem q = p;
-  q.rows2_tile = rows2_tile;
+  q.rows2_tile = 0;
+  auto tile = [&](FwdEpilogue epi) {
+    const FwdSizes sizes{cu_count(), p.N, p.K, p.offsets ? p.groups : 1, p.rows_hint, p.rows2};
+    const Tile t = fwd_tile(sizes, epi);
+    if (p.epi != EPI_SWIGLU_BWD) q.rows2_tile = extra_group_rows(sizes, epi, t);
+    return t;
+  };
   switch (p.epi) {
-    case EPI_SWIGLU: return launch_cfg<EPI_SWIGLU>(cfg_swiglu, q, stream);
-    case EPI_SWIGLU_BWD:
+    case EPI_SWIGLU: return launch_cfg<EPI_SWIGLU>(tile(FWD_SWIGLU), q, stream);
+    case EPI_SWIGLU_BWD:                                   // the forward up-projection's tiles (same operand shapes)
       if (!p.dact || !p.act_out || p.rows2 > 0 || p.ldy != 2 * (int64_t)p.N) return hipErrorInvalidValue;
-      switch (cfg_swiglu_bwd) {      // the tiers of the forward up-projection (same operand shapes)
-        case 20: return launch_tile<64, 128, 64, 3, 2, 2, EPI_SWIGLU_BWD>(p, stream);
-        case 5: return launch_tile<128, 256, 64, 3, 2, 4, EPI_SWIGLU_BWD>(p, stream);
-        case 8: return launch_phase_gemm(320, p, stream);
-        default: return launch_phase_gemm(256, p, stream);
-      }
-    case EPI_BF16: return launch_cfg<EPI_BF16>(cfg_bf16, q, stream);
+      return launch_cfg<EPI_SWIGLU_BWD>(tile(FWD_SWIGLU), q, stream);
+    case EPI_BF16: return launch_cfg<EPI_BF16>(tile(FWD_BF16), q, stream);
     case EPI_SCATTER:
       if (p.scatter_rows < 1) return hipErrorInvalidValue;
-      switch (tier) {      // the tiers of the bf16 epilogue (same operand shapes)
-        case 20: return launch_tile<64, 128, 64, 3, 2, 2, EPI_SCATTER>(p, stream);
-        case 5: return launch_tile<128, 256, 64, 3, 2, 4, EPI_SCATTER>(p, stream);
-        default: return launch_phase_gemm(256, p, stream);
-      }
+      return launch_cfg<EPI_SCATTER>(tile(FWD_SCATTER), q, stream);
     case EPI_F32:
     {
       const TileShape ft = f32_tile(p.offsets ? p.max_rows : p.rows_single, p.N);

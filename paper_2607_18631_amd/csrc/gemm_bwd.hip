@@ -31,8 +31,6 @@
 // Persistent workgroups walk the tile list; the next tile's first slice is in flight during
 // the epilogue.  K tails (segments of any length) are fetched from clamped addresses and
 // zeroed in LDS; rows / columns past the edges are clamped and never stored.
-#include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
@@ -40,6 +38,7 @@
 #include "gemm_device.hpp"
 #include "gemm_phase_bwd.hpp"
 #include "kernels.hpp"
+#include "tile_rule.hpp"
 
 namespace moe {
 namespace {
@@ -434,45 +433,16 @@ hipError_t launch_gemm_bwd(const GemmBwdProblem& p, hipStream_t stream) {
     // K a multiple of 64 (every expert and shared dimension of the measured workloads): the
     // instances without K-tail code, which also leave the registers the 320-row tile needs
     const bool kt = p.K % 64 != 0;
-    if (p.rows_hint > 0 && p.rows_hint <= 128)
-      return kt ? launch_bwd<64, 128, 64, 3, 2, 2, false, true, BWD_ROWS, 1, true>(p, stream)
-                : launch_bwd<64, 128, 64, 3, 2, 2, false, true, BWD_ROWS, 1, false>(p, stream);
-    // Tile shapes (all on the MN-major weight operand, two ds_read_b64_tr_b16 per fragment):
-    // 256 x 256 over 2 x 4 waves, a wave holding 128 token rows x 64 weight columns, so a K-step
-    // reads four token fragments (ds_read_b128) and two weight fragments, against two and four
-    // with 4 x 2 waves -- the transpose reads are the dearer ones (DeepSeek-V3 routed dX 816 ->
-    // 634 us, shared dX 605 -> 481); 256 x 128 (4 x 2 waves); 320 x 256 (2 x 4 waves, 10 token
-    // blocks).  Chosen like the forward's tiles, from the expected tile count of each shape: a
-    // persistent launch takes about ceil(tiles / CUs) rounds, a 256 x 128 tile costs ~0.6 of a
-    // 256 x 256 one and a 320-row tile ~1.15, and an expert's rows scatter around their mean with a
-    // standard deviation of about its square root (at 256 rows per expert: 1.5 256-row m-tiles on
-    // average, one 320-row tile).
-    const double cus = cu_count();
-    const double mu = p.rows_hint > 0 ? (double)p.rows_hint : (double)p.max_rows / p.groups;
-    const double sigma = p.groups > 1 ? std::sqrt(mu) : 0.0;
-    auto mtiles = [&](int bm) {
-      double per_group = 0;
-      if (sigma == 0) {
-        per_group = std::ceil(mu / bm);
-      } else {
-        const int jmax = (int)((mu + 8 * sigma) / bm) + 1;
-        for (int j = 0; j <= jmax; ++j)                   // E[ceil(m / bm)] = sum_j P(m > j bm)
-          per_group += 0.5 * std::erfc((j * bm - mu) / (sigma * std::sqrt(2.0)));
-      }
-      return per_group * p.groups;
-    };
-    // rounds of the persistent grid; an expected count a few hundredths of a round above a
-    // whole number (the normal tail of the row counts) is that whole number
-    auto rounds = [&](double tiles) { return std::max(1.0, std::ceil(tiles / cus - 0.05)); };
-    const double tn256 = (double)((p.N + 255) / 256), tn128 = (double)((p.N + 127) / 128);
-    const double c1 = rounds(mtiles(256) * tn256), c2 = 0.6 * rounds(mtiles(256) * tn128);
-    const double c3 = kt ? 1e30 : 1.15 * rounds(mtiles(320) * tn256);   // no tail instance of it
-    const int cfg = (c3 < c1 && c3 <= c2) ? 3 : c2 < c1 ? 2 : 1;
-    if (cfg == 3) return launch_phase_bwd(320, p, stream);
-    if (cfg == 2)
-      return kt ? launch_bwd<256, 128, 64, 3, 4, 2, false, true, BWD_ROWS, 1, true>(p, stream)
-                : launch_bwd<256, 128, 64, 3, 4, 2, false, true, BWD_ROWS, 1, false>(p, stream);
-    return launch_phase_bwd(256, p, stream);
+    switch (bwd_rows_tile(cu_count(), p.groups, p.rows_hint, p.max_rows, p.N, p.K)) {
+      case TILE_64X128:
+        return kt ? launch_bwd<64, 128, 64, 3, 2, 2, false, true, BWD_ROWS, 1, true>(p, stream)
+                  : launch_bwd<64, 128, 64, 3, 2, 2, false, true, BWD_ROWS, 1, false>(p, stream);
+      case TILE_256X128:
+        return kt ? launch_bwd<256, 128, 64, 3, 4, 2, false, true, BWD_ROWS, 1, true>(p, stream)
+                  : launch_bwd<256, 128, 64, 3, 4, 2, false, true, BWD_ROWS, 1, false>(p, stream);
+      case TILE_320X256: return launch_phase_bwd(320, p, stream);
+      default: return launch_phase_bwd(256, p, stream);
+    }
   }
   if (p.mode == BWD_KSEG) {
     // weight gradients: both operands row-major activations reduced over the group's rows

@@ -1,0 +1,116 @@
+// Which tile each grouped-GEMM launch runs on: rules on sizes only, host code without HIP.
+#pragma once
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+namespace moe {
+
+// token rows x weight rows (a SwiGLU tile's weight rows are half gate, half up)
+enum Tile { TILE_64X128, TILE_128X256, TILE_256X128, TILE_256X256, TILE_320X256 };
+
+// Expected tiles of `groups` row segments of about `rows` rows each.  The per-expert row counts of a
+// routed batch scatter around their mean (standard deviation about its square root), so an expert
+// whose mean is 256 rows takes 1.5 256-row m-tiles on average but one 320-row tile.
+inline double expected_mtiles(int bm, double rows, int64_t groups) {
+  if (groups <= 1 || rows <= 0) return std::ceil(rows / bm) * groups;
+  const double sigma = std::sqrt(rows);
+  double per_group = 0;
+  const int jmax = (int)((rows + 8 * sigma) / bm) + 1;
+  for (int j = 0; j <= jmax; ++j)                          // E[ceil(m / bm)] = sum_j P(m > j bm)
+    per_group += 0.5 * std::erfc((j * bm - rows) / (sigma * std::sqrt(2.0)));
+  return per_group * groups;
+}
+// rounds of a persistent grid of one workgroup per CU; an expected count a few hundredths of a round
+// above a whole number (the normal tail of the row counts) is that whole number
+inline double tile_rounds(double tiles, int cus) { return std::max(1.0, std::ceil(tiles / cus - 0.05)); }
+
+enum FwdEpilogue { FWD_SWIGLU, FWD_BF16, FWD_SCATTER };
+// A forward launch (also the backward's recomputed up-projection): `groups` row segments (1: dense rows)
+// of about rows_hint rows (0: unknown), rows2 rows of the extra dense group, N outputs, reduction K.
+struct FwdSizes {
+  int cus;
+  int N, K;
+  int64_t groups, rows_hint, rows2;
+};
+
+// 256 x 256 tiles of the phase kernel: the best measured on the DeepSeek-V3, Mixtral and skewed
+// workloads (largest reuse per byte copied into LDS; also whenever a large dense extra group shares
+// the launch).  With few expected rows per group the launch is a
+// weight stream over few m-tiles, spread over more workgroups by smaller tiles: 64 x 128 up to
+// 128 rows per group (1.4-1.8x faster at 2-128 rows), 128 x 256 up to 512 (1.1-1.5x).
+inline Tile fwd_tile(const FwdSizes& s, FwdEpilogue epi) {
+  const Tile tier = s.rows_hint <= 0 || s.rows2 > 512 ? TILE_256X256
+                    : s.rows_hint <= 128              ? TILE_64X128
+                    : s.rows_hint <= 512              ? TILE_128X256
+                                                      : TILE_256X256;
+  if (tier == TILE_64X128 || s.rows_hint <= 0 || epi == FWD_SCATTER) return tier;
+  // Tile shape from the expected tile count of each shape.  A persistent launch takes about
+  // ceil(tiles / CUs) rounds of its slowest workgroup; per tile, a 320 x 256 tile (10 token
+  // blocks, 2 x 4 waves) costs ~1.15 of a 256 x 256 one, a 128 x 256 tile ~0.7, a 256 x 128 tile
+  // ~0.6 (measured).  DeepSeek-V3 shapes (256 rows per expert,
+  // shared expert of 8192 rows in the launch) run both projections on 320-row tiles (up
+  // 1085-1093 -> 1000-1025 us, down 588-596 -> 565-568), Mixtral shapes (1024 rows per expert,
+  // 2.25 rounds of 256 x 256 down-projection tiles) their down-projection (1137-1147 -> 944-955;
+  // 256 x 128 tiles: 1097), while Mixtral's up-projection (15.75 rounds either way) and the
+  // skewed workload stay on 256 x 256.  The backward's recomputed up-projection of the routed
+  // experts alone (tier 128 x 256) takes 320-row tiles at DeepSeek-V3 (627 -> 521 us).
+  auto mtiles = [&](int bm) {
+    return expected_mtiles(bm, (double)s.rows_hint, s.groups) + std::ceil((double)s.rows2 / bm);
+  };
+  auto rounds = [&](double tiles) { return tile_rounds(tiles, s.cus); };
+  const double tn128 = (double)((s.N + 127) / 128);        // 128-column output blocks
+  // a 256-row weight tile yields 128 SwiGLU outputs
+  const double tn = epi == FWD_SWIGLU ? tn128 : std::ceil(tn128 / 2);
+  const double m128 = mtiles(128), m256 = mtiles(256), m320 = mtiles(320);
+  // A launch whose 256-row tiles cover at most a quarter of the chip takes 64 x 128 ones, an eighth of
+  // the work each and two workgroups per CU, so they still fit about one round.  3001 rows x a
+  // shared expert of F = 264, d = 2040: up-projection 36 tiles of 256 x 256 109 us, 235 of 64 x 128 26 us.
+  if (tier == TILE_256X256 && s.rows2 == 0 && m256 * tn <= s.cus / 4.0) return TILE_64X128;
+  // bf16 epilogue: no 320-row tiles with a K tail (that instance
+  // reloads spilled registers next to its K loops, whose waits then cover every copy in flight)
+  const double c320 = epi == FWD_BF16 && s.K % 64 ? 1e30 : 1.15 * rounds(m320 * tn);
+  if (tier == TILE_128X256) return c320 < 0.7 * rounds(m128 * tn) ? TILE_320X256 : tier;
+  const double c256 = rounds(m256 * tn);
+  // bf16 epilogue: also 256 x 128 tiles
+  const double c256x128 = epi == FWD_BF16 ? 0.6 * rounds(m256 * tn128) : 1e30;
+  if (c320 < c256 && c320 <= c256x128) return TILE_320X256;
+  return c256x128 < c256 ? TILE_256X128 : tier;
+}
+
+// Rows of the extra group's tiles in a launch on `tile`, 0 for that tile's own.  On 320-row tiles, a
+// dense extra group (the shared expert) is tiled 256 rows high when that
+// adds no round: its tiles then carry the 8 live token blocks the routed ones do (the routed
+// experts' ~256 rows), instead of 10.  DeepSeek-V3 shapes: up-projection 928 -> 1024 tiles
+// (4 rounds either way), down-projection 1624 -> 1792 (7 rounds either way).
+inline int extra_group_rows(const FwdSizes& s, FwdEpilogue epi, Tile tile) {
+  if (tile != TILE_320X256 || s.rows2 <= 256) return 0;
+  const double cols = (double)(epi == FWD_SWIGLU ? (s.N + 127) / 128 : (s.N + 255) / 256);
+  const double g320 = expected_mtiles(320, (double)s.rows_hint, s.groups);
+  return tile_rounds((g320 + std::ceil(s.rows2 / 256.0)) * cols, s.cus) <=
+                 tile_rounds((g320 + std::ceil(s.rows2 / 320.0)) * cols, s.cus)
+             ? 256
+             : 0;
+}
+
+// The backward's row products (dA, dX): max_rows rows in all.
+// Tile shapes (all on the MN-major weight operand, two ds_read_b64_tr_b16 per fragment):
+// 256 x 256 over 2 x 4 waves, a wave holding 128 token rows x 64 weight columns, so a K-step
+// reads four token fragments (ds_read_b128) and two weight fragments, against two and four
+// with 4 x 2 waves -- the transpose reads are the dearer ones (DeepSeek-V3 routed dX 816 ->
+// 634 us, shared dX 605 -> 481); 256 x 128 (4 x 2 waves); 320 x 256 (2 x 4 waves, 10 token
+// blocks).  Chosen like the forward's tiles, from the expected tile count of each shape; no 320-row
+// tiles with a K tail.
+inline Tile bwd_rows_tile(int cus, int64_t groups, int64_t rows_hint, int64_t max_rows, int N, int K) {
+  if (rows_hint > 0 && rows_hint <= 128) return TILE_64X128;
+  const double rows = rows_hint > 0 ? (double)rows_hint : (double)max_rows / groups;
+  auto cost = [&](int bm, int bn) {
+    return tile_rounds(expected_mtiles(bm, rows, groups) * ((N + bn - 1) / bn), cus);
+  };
+  const double c256 = cost(256, 256), c256x128 = 0.6 * cost(256, 128);
+  const double c320 = K % 64 ? 1e30 : 1.15 * cost(320, 256);
+  if (c320 < c256 && c320 <= c256x128) return TILE_320X256;
+  return c256x128 < c256 ? TILE_256X128 : TILE_256X256;
+}
+
+}  // namespace moe

@@ -19,11 +19,19 @@ from parity_util import REL_TOL, dev_bits, rel_fro
 pytestmark = pytest.mark.gpu
 
 COUNTS = [0, 1, 31, 32, 33, 64, 65, 97, 129, 160, 191, 225, 255, 256, 257, 319, 321] * 2
+# reductions of one to four or more K slices, without and with a partial last one
+WIDTHS = [64, 128, 192, 256] + [40, 72, 136, 200]
+# (capacity per expert, d, F, tile of the up-projection, of the down-projection); test_tile_rule.py checks the tiles
+SEGMENTS = ([(600, d, 136, "256x256", "256x256" if d >= 320 else "256x128") for d in WIDTHS + [456]] +
+            [(700, 1024, F, "256x256", "256x256") for F in WIDTHS + [640]] +
+            [(280, d, 640, "320x256", "128x256") for d in WIDTHS + [456]] +
+            [(300, 1792, F, "128x256", "320x256") for F in WIDTHS[:4]])
+FEW_TILES = [(3001, 200, 264), (513, 64, 8), (1000, 1032, 40)]
 
 
-@pytest.mark.parametrize("rows_hint, F", [(600, 136), (700, 640)], ids=["tile256", "tile320"])
-@pytest.mark.parametrize("d", [64, 72, 128, 192, 200, 456])
-def test_segment_ends_and_slice_counts(rows_hint, F, d):
+@pytest.mark.parametrize("case", SEGMENTS, ids=str)
+def test_segment_ends_and_slice_counts(case):
+    rows_hint, d, F, _, _ = case
     E = len(COUNTS)
     sh = wl.MoEShape(T=rows_hint * E, d=d, E=E, top_k=1, F=F, E_local=E)
     offs = np.concatenate([[0], np.cumsum(COUNTS)]).astype(np.int32)
@@ -47,7 +55,7 @@ def test_segment_ends_and_slice_counts(rows_hint, F, d):
             assert rel_fro(got[a:b], ref) <= REL_TOL, (e, COUNTS[e])
 
 
-@pytest.mark.parametrize("T, d, F", [(3001, 200, 264), (513, 64, 8), (1000, 1032, 40)])
+@pytest.mark.parametrize("T, d, F", FEW_TILES)
 def test_few_large_tiles_take_small_ones(T, d, F):
     """One dense segment whose 256-row tiles would cover at most a quarter of the chip runs on 64-row tiles:
     the same results, bit for bit, as the rows in groups of at most 128 (the small tiles of such groups)."""
@@ -69,15 +77,22 @@ def test_few_large_tiles_take_small_ones(T, d, F):
     assert np.array_equal(outs[0], outs[1])
 
 
-def test_backward_slice_counts_between_tiles():
+BACKWARD_COUNTS = [0, 5, 193, 250, 64, 256, 65, 300, 128, 129, 192, 420] * 4
+# (capacity per expert, d, F, tile of dX); test_tile_rule.py checks the tile
+BACKWARD = [(200, 1000, 504, "256x256"), (280, 1024, 512, "320x256")]
+
+
+@pytest.mark.parametrize("rows_hint, d, F, tile", BACKWARD)
+def test_backward_slice_counts_between_tiles(rows_hint, d, F, tile):
     """moe_grouped_ffn_backward on 48 segments of none to seven 64-row slices in turn, with more weight-gradient
     tiles than workgroups: a tile's last slices issue the next tile's first ones when both have three or
     more, and every change between such tiles, shorter ones and empty ones follows another.  Output
-    edges cut tiles in both directions, and the row products' reductions end in a partial slice.  Each
+    edges cut tiles in both directions, and the row products' reductions end in a partial slice; the second case's
+    dX runs on 320-row tiles (which take no partial slice).  Each
     gradient within rel. Frobenius 5e-3 (bf16 results of at most two bf16 intermediates)."""
-    counts = [0, 5, 193, 250, 64, 256, 65, 300, 128, 129, 192, 420] * 4
-    E, d, F = len(counts), 1000, 504
-    sh = wl.MoEShape(T=200 * E, d=d, E=E, top_k=1, F=F, E_local=E)
+    counts = BACKWARD_COUNTS
+    E = len(counts)
+    sh = wl.MoEShape(T=rows_hint * E, d=d, E=E, top_k=1, F=F, E_local=E)
     offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     n = int(offs[-1])
     rng = np.random.default_rng(3)

@@ -1,0 +1,64 @@
+"""The sizes on which the GPU tests of the large-tile GEMMs run do reach the tiles they name: the rules of
+tile_rule.hpp, compiled for the host, evaluated for the 256 CUs of an MI355X.  A change of a rule that empties
+one of those tests fails here."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_phase_gemm as phase
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2607_18631_amd", "csrc")
+CUS = 256
+TILES = ["64x128", "128x256", "256x128", "256x256", "320x256"]
+SWIGLU, BF16, SCATTER = range(3)
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rule") / "rule.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    os.path.join(HERE, "tile_rule.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    i, l = ctypes.c_int, ctypes.c_long
+    lib.fwd_tile.argtypes = [i, i, i, l, l, l, i]
+    lib.bwd_rows_tile.argtypes = [i, l, l, l, i, i]
+    return lib
+
+
+@pytest.mark.parametrize("case", phase.SEGMENTS, ids=str)
+def test_segment_cases_reach_their_tiles(rule, case):
+    """moe_grouped_ffn passes the capacity per local expert as the expected rows."""
+    rows, d, F, up, down = case
+    E = len(phase.COUNTS)
+    assert TILES[rule.fwd_tile(CUS, F, d, E, rows, 0, SWIGLU)] == up
+    assert TILES[rule.fwd_tile(CUS, d, F, E, rows, 0, BF16)] == down
+
+
+def test_segment_cases_cover_both_schedules():
+    """Each tile height with one, two, three and more K slices, with and without a partial last one, wherever an
+    instance exists (no 320-row tile with a partial slice in the down-projection)."""
+    slices = lambda K: (min(-(-K // 64), 4), K % 64 != 0)
+    up = {(c[3], *slices(c[1])) for c in phase.SEGMENTS}
+    down = {(c[4], *slices(c[2])) for c in phase.SEGMENTS}
+    for n in (1, 2, 3, 4):
+        for tail in (False, True):
+            for have, tile in ((up, "256x256"), (down, "256x256"), (up, "320x256")) + (() if tail else ((down, "320x256"),)):
+                assert (tile, n, tail) in have, (tile, n, tail)
+
+
+def test_few_tile_cases_reach_the_small_tile(rule):
+    for T, d, F in phase.FEW_TILES:
+        assert TILES[rule.fwd_tile(CUS, F, d, 1, T, 0, SWIGLU)] == "64x128"
+        assert TILES[rule.fwd_tile(CUS, d, F, 1, T, 0, BF16)] == "64x128"
+
+
+def test_backward_cases_reach_their_tiles(rule):
+    E = len(phase.BACKWARD_COUNTS)
+    for rows, d, F, tile in phase.BACKWARD:
+        assert TILES[rule.bwd_rows_tile(CUS, E, rows, rows * E, d, 2 * F)] == tile

@@ -1,0 +1,11 @@
+// The tile rules of the grouped GEMMs as a C library for test_tile_rule.py.
+#include "tile_rule.hpp"
+
+extern "C" {
+int fwd_tile(int cus, int N, int K, long groups, long rows_hint, long rows2, int epilogue) {
+  return moe::fwd_tile({cus, N, K, groups, rows_hint, rows2}, (moe::FwdEpilogue)epilogue);
+}
+int bwd_rows_tile(int cus, long groups, long rows_hint, long max_rows, int N, int K) {
+  return moe::bwd_rows_tile(cus, groups, rows_hint, max_rows, N, K);
+}
+}
