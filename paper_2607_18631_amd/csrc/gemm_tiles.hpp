@@ -243,10 +243,16 @@ struct CopyPlan {
   static constexpr int L = LX + LW;                        // vector-memory ops per wave per slice
   static_assert(LX >= 1 && LW >= 1 && (BM / RPI) % NW == 0 && (BN / RPI) % NW == 0, "tile too small");
 
+  // The lanes past K as a scalar mask, or compared from the lane's chunk at each copy.  On 320-row tiles the allocator
+  // fits only one of the two without copies of fragments around the K loop's back edge: 16 experts of 629 rows, d = 4768,
+  // F = 3416, SwiGLU backward 660 us with the mask and 792 without, SwiGLU 742 and 593.
+  static constexpr bool PAST_MASK = EPI == EPI_SWIGLU_BWD;
+
   const char* xbase;
   const char* wsb[LW];
   uint32_t xoff[LX], woff[LW];
   int xchunk[LX], wchunk[LW];
+  uint64_t past;                                           // lanes whose chunk of the partial last slice lies past K
 
   __device__ __forceinline__ void setup(const GemmProblem& p, const TileDesc& t, int wave, int lane) {
     const int li_row = lane / Z::CPR, li_pc = lane % Z::CPR;
@@ -272,6 +278,8 @@ struct CopyPlan {
         xoff[j] = (uint32_t)(min(r, last) * p.ldx * 2 + xchunk[j] * 16);
       }
     }
+    // every copy of a lane has the same chunk (the swizzle repeats every 16 rows)
+    if constexpr (PAST_MASK) past = __ballot((K - 1) / BK * BK + xchunk[0] * 8 >= K);
 #pragma unroll
     for (int j = 0; j < LW; ++j) {
       const int r = (wave + NW * j) * RPI + li_row;
@@ -333,12 +341,18 @@ struct CopyPlan {
     if constexpr (!KT) {
       issue_one_sv<J>(dst, kt, wave);
     } else {
-      const int k0b = kt * BK * 2;
-      const char* src;
-      if constexpr (J < LX) src = xbase + k0b + xoff[J];
-      else src = wsb[J - LX] + k0b + woff[J - LX];
-      // every copy of a lane has the same chunk (the swizzle repeats every 16 rows)
-      if (kt * BK + xchunk[0] * 8 >= K) src = reinterpret_cast<const char*>(g_zero_chunk);
+      const uint64_t base = (uint64_t)(J < LX ? xbase : wsb[J < LX ? 0 : J - LX]) + kt * BK * 2;
+      const uint32_t off = J < LX ? xoff[J < LX ? J : 0] : woff[J < LX ? 0 : J - LX];
+      // added in halves: for a 64-bit sum the compiler holds every offset widened to 64 bits over the K loop, and
+      // reloads them from scratch between its MFMAs
+      uint32_t lo = (uint32_t)base;
+      asm volatile("" : "+s"(lo));
+      const uint32_t sum = lo + off;
+      const char* src = reinterpret_cast<const char*>((uint64_t)((uint32_t)(base >> 32) + (sum < off)) << 32 | sum);
+      bool dead;
+      if constexpr (PAST_MASK) dead = __builtin_amdgcn_inverse_ballot_w64(past);
+      else dead = kt * BK + xchunk[0] * 8 >= K;
+      if (dead) src = reinterpret_cast<const char*>(g_zero_chunk);
       dma16_v(src, dst + (J < LX ? (wave + NW * J) * 512 : BM * BK + (wave + NW * (J - LX)) * 512));
     }
   }

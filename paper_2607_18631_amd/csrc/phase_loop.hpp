@@ -96,7 +96,6 @@ struct PhaseTile {
   __device__ __forceinline__ static int slot(int s) { return s * SLICE; }
   __device__ __forceinline__ bf16x8 tr(int off) const {
     typedef short v4s __attribute__((ext_vector_type(4)));
-    typedef short v8s __attribute__((ext_vector_type(8)));
     typedef __attribute__((address_space(3))) v4s lds_v4s;
     const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(ring + off));
     const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(ring + off + 4 * 64));
@@ -260,6 +259,11 @@ __device__ __forceinline__ void phase_loop(const PT& pt, const CP& cp, f32x4 (&a
     // it does not need yet
     __builtin_amdgcn_s_waitcnt(0xc07f);                    // lgkmcnt(0)
   }
+  // The slot of the loop's last slices follows from nl alone, which is the same for every tile of a forward launch: not
+  // hidden from the compiler, their LDS addresses are computed once per launch, spilled, and reloaded between
+  // the MFMAs, each reload waiting for the copies in flight (43 on a 320-row tile, 3 this way; 32 experts of
+  // 320 rows, F = 640, d = 6144: down-projection 146 -> 128 us).
+  if constexpr (!STREAM) asm volatile("" : "+s"(s0));
   int i = 0;
   for (; i < nl - RMAX; ++i) slice(std::integral_constant<int, RMAX>{}, i);
   if constexpr (RMAX == 3)

@@ -58,7 +58,12 @@ def device_asm(tmp_path_factory):
     return dict(zip(srcs, texts))
 
 
-@pytest.mark.parametrize("src", ["gemm.hip", "gemm_bwd.hip"])
+def _tile_code(lines):
+    """Code of the tile loop: an epilogue's stores, or the accumulators' zeroing."""
+    return any("global_store" in l for l in lines) or sum(bool(re.search(r"v_mov_b(32|64)\S* v(\d+|\[\d+:\d+\]), ", l)) for l in lines) > 16
+
+
+@pytest.mark.parametrize("src", ["gemm.hip", "gemm_phase.hip", "gemm_bwd.hip"])
 def test_no_scratch_in_mfma_loops(device_asm, src):
     funcs = re.split(r"\n(?=_Z\S+:)", device_asm[src])
     checked = 0
@@ -68,12 +73,45 @@ def test_no_scratch_in_mfma_loops(device_asm, src):
         name = f.split(":", 1)[0]
         lines = f.split("\n")
         loops = _mfma_loops(lines)
+        if src == "gemm_phase.hip":
+            # one K loop per count of phases and live blocks; the code around them (the last slices of each) is
+            # laid out with backward branches too
+            loops = [(a, b) for a, b in loops if not _tile_code(lines[a:b + 1])]
         assert loops, f"no MFMA loop found in {name}"
         inside = [lines[i].strip() for a, b in loops for i in range(a, b + 1) if "scratch_" in lines[i]]
         assert not inside, f"{name}: scratch accesses inside an MFMA loop: {inside[:4]}"
         checked += 1
     assert checked >= 8, f"only {checked} MFMA kernels found in {src}"
     print(f"[codegen] {src}: {checked} MFMA kernels, no scratch access inside their K loops")
+
+
+def _reloads_between_mfmas(lines, near=30):
+    """Scratch loads with an MFMA within `near` instructions on both sides."""
+    ins = [l.split(";")[0].strip() for l in lines]
+    ins = [l for l in ins if l and not l.startswith(".") and not l.endswith(":")]
+    mfma = [i for i, l in enumerate(ins) if l.startswith("v_mfma")]
+    close = lambda i: any(0 < i - m <= near for m in mfma) and any(0 < m - i <= near for m in mfma)
+    return sum(l.startswith("scratch_load") and close(i) for i, l in enumerate(ins))
+
+
+@pytest.mark.parametrize("src", ["gemm_phase.hip", "gemm_bwd.hip"])
+def test_few_reloads_between_mfmas(device_asm, src):
+    """A reload between MFMAs waits for the copies in flight, in a tile's last slices as well as in its K loop.  At most
+    the four fragment offsets, once per tile, behind the K loop."""
+    checked = 0
+    for f in re.split(r"\n(?=_Z\S+:)", device_asm[src]):
+        if "v_mfma" in f and "k_phase" in f.split(":", 1)[0]:
+            n = _reloads_between_mfmas(f.split("\n"))
+            assert n <= 4, f"{f.split(':', 1)[0]}: {n} reloads between MFMAs"
+            checked += 1
+    assert checked >= 4
+
+
+def test_reload_finder():
+    m, load = "\tv_mfma_f32_16x16x32_bf16 v[0:3]", "\tscratch_load_dword v3, off, off offset:36 ; 4-byte Folded Reload"
+    far = ["\tv_mov_b32_e32 v1, v2"] * 40
+    assert _reloads_between_mfmas([m, load, "\ts_waitcnt vmcnt(0)", m]) == 1
+    assert _reloads_between_mfmas([m, load, *far, m]) == 0 and _reloads_between_mfmas([m, *far, load, m]) == 0
 
 
 def _m0_hazards(lines):
