@@ -67,9 +67,9 @@ inline Tile fwd_tile(const FwdSizes& s, FwdEpilogue epi) {
   // the work each and two workgroups per CU, so they still fit about one round.  3001 rows x a
   // shared expert of F = 264, d = 2040: up-projection 36 tiles of 256 x 256 109 us, 235 of 64 x 128 26 us.
   if (tier == TILE_256X256 && s.rows2 == 0 && m256 * tn <= s.cus / 4.0) return TILE_64X128;
-  // bf16 epilogue: no 320-row tiles with a K tail (that instance
-  // reloads spilled registers next to its K loops, whose waits then cover every copy in flight)
-  const double c320 = epi == FWD_BF16 && s.K % 64 ? 1e30 : 1.15 * rounds(m320 * tn);
+  // With a partial last K slice too: 32 experts of 256 rows, d = F = 2040: up-projection 174 us on 320-row tiles, 274 on
+  // 128 x 256, down-projection 96 and 152; 8 experts of 569 rows, d = 6408, F = 6112: up 633 and 842 (256 x 256), down 355 and 408.
+  const double c320 = 1.15 * rounds(m320 * tn);
   if (tier == TILE_128X256) return c320 < 0.7 * rounds(m128 * tn) ? TILE_320X256 : tier;
   const double c256 = rounds(m256 * tn);
   // bf16 epilogue: also 256 x 128 tiles

@@ -25,7 +25,7 @@ WIDTHS = [64, 128, 192, 256] + [40, 72, 136, 200]
 SEGMENTS = ([(600, d, 136, "256x256", "256x256" if d >= 320 else "256x128") for d in WIDTHS + [456]] +
             [(700, 1024, F, "256x256", "256x256") for F in WIDTHS + [640]] +
             [(280, d, 640, "320x256", "128x256") for d in WIDTHS + [456]] +
-            [(300, 1792, F, "128x256", "320x256") for F in WIDTHS[:4]])
+            [(300, 1792, F, "128x256", "320x256") for F in WIDTHS])
 FEW_TILES = [(3001, 200, 264), (513, 64, 8), (1000, 1032, 40)]
 
 

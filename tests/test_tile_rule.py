@@ -41,15 +41,14 @@ def test_segment_cases_reach_their_tiles(rule, case):
 
 
 def test_segment_cases_cover_both_schedules():
-    """Each tile height with one, two, three and more K slices, with and without a partial last one, wherever an
-    instance exists (no 320-row tile with a partial slice in the down-projection)."""
+    """Each tile height with one, two, three and more K slices, with and without a partial last one."""
     slices = lambda K: (min(-(-K // 64), 4), K % 64 != 0)
     up = {(c[3], *slices(c[1])) for c in phase.SEGMENTS}
     down = {(c[4], *slices(c[2])) for c in phase.SEGMENTS}
     for n in (1, 2, 3, 4):
         for tail in (False, True):
-            for have, tile in ((up, "256x256"), (down, "256x256"), (up, "320x256")) + (() if tail else ((down, "320x256"),)):
-                assert (tile, n, tail) in have, (tile, n, tail)
+            for tile in ("256x256", "320x256"):
+                assert (tile, n, tail) in up and (tile, n, tail) in down, (tile, n, tail)
 
 
 def test_few_tile_cases_reach_the_small_tile(rule):
@@ -62,3 +61,12 @@ def test_backward_cases_reach_their_tiles(rule):
     E = len(phase.BACKWARD_COUNTS)
     for rows, d, F, tile in phase.BACKWARD:
         assert TILES[rule.bwd_rows_tile(CUS, E, rows, rows * E, d, 2 * F)] == tile
+
+
+def test_a_partial_slice_keeps_the_tile(rule):
+    """The forward's tile follows from the tile counts; a K that is no multiple of 64 does not change it."""
+    for E, rows, N in [(32, 256, 2048), (32, 290, 6384), (64, 227, 3184), (8, 569, 6408), (64, 400, 1000)]:
+        for epilogue in (SWIGLU, BF16):
+            tiles = {TILES[rule.fwd_tile(CUS, N, K, E, rows, 0, epilogue)] for K in (2040, 2048, 2056)}
+            assert len(tiles) == 1, (E, rows, N, epilogue, tiles)
+    assert TILES[rule.fwd_tile(CUS, 2040, 2040, 32, 256, 0, BF16)] == "320x256"
