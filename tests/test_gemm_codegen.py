@@ -114,6 +114,17 @@ def test_reload_finder():
     assert _reloads_between_mfmas([m, load, *far, m]) == 0 and _reloads_between_mfmas([m, *far, load, m]) == 0
 
 
+def test_weight_gradients_are_stored_nontemporally(device_asm):
+    """Every 16-byte store of the large-tile weight-gradient kernel, an empty group's zeros too: they are written
+    once and not read again by the step, and must not displace its weights in the last-level cache."""
+    f = [f for f in re.split(r"\n(?=_Z\S+:)", device_asm["gemm_bwd.hip"])
+         if "k_phase_bwdILi256ELi1E" in f.split(":", 1)[0] and "v_mfma" in f]
+    assert len(f) == 1
+    stores = [l.strip() for l in f[0].split("\n") if "global_store_dwordx4" in l]
+    assert len(stores) >= 17
+    assert not [l for l in stores if not re.search(r"\bnt\b", l)]
+
+
 def _m0_hazards(lines):
     """Direct-to-LDS loads whose very next preceding instruction writes M0 by a scalar instruction."""
     found, prev = [], ""
