@@ -352,6 +352,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_bwd(GemmBwdProblem
     // at piece c ^ (r % (WN / 8)), spreading the 32 rows a write instruction touches over the
     // banks.
     bf16_t* yg = p.Y + (MODE == BWD_KSEG ? (int64_t)cur.g * p.y_group_stride : 0);
+    if constexpr (MODE == BWD_KSEG && BN == 256) {
+      static_assert(NTH == 512, "store_zero_tile");
+      if (cur.klen == 0) {
+        store_zero_tile<BM>(yg, p.ldy, cur.m0, cur.m_end, cur.n0, p.N, wave, lane);
+        if (!more) break;
+        continue;
+      }
+    }
     bf16_t* st_area = ring + (STAGES - 1) * SLICE + wave * 32 * WN;
     constexpr int CPRW = WN / 8;                          // 16-byte pieces per staged row
 #pragma unroll
@@ -447,11 +455,12 @@ hipError_t launch_gemm_bwd(const GemmBwdProblem& p, hipStream_t stream) {
   if (p.mode == BWD_KSEG) {
     // weight gradients: both operands row-major activations reduced over the group's rows
     if (!p.x_mn || !p.w_mn || p.M < 8 || p.M % 8) return hipErrorInvalidValue;
-    // 256 x 256 tiles of the phase kernel
     // the router's weight gradient (float32 K-split partials, M = the expert count): 128 x 128
     // tiles, two workgroups per CU, 4x the tiles of 256 x 256 ones for its few output tiles
     // (DeepSeek-V3: 256 x 7168 outputs over 9 token chunks, 76 -> 59 us)
     if (p.Yf) return launch_bwd<128, 128, 64, 2, 2, 2, true, true, BWD_KSEG, 2>(p, stream);
+    if (wgrad_on_ring(p.rows_hint, p.ldy))
+      return launch_bwd<256, 256, 64, 2, 4, 2, true, true, BWD_KSEG, 1>(p, stream);
     return launch_phase_bwd(256, p, stream);
   }
   return hipErrorInvalidValue;

@@ -205,16 +205,7 @@ __global__ __launch_bounds__(512, 1) void k_phase_bwd(GemmBwdProblem p) {
     bf16_t* y = p.Y + (KSEG ? (int64_t)cur.g * p.y_group_stride : 0);
     const int row0 = cur.m0 + wm * 32, col0 = cur.n0 + wn * 64;
     if (KSEG && cur_nl == 0) {
-      // A group without rows: zeros, two 512-byte row pieces per instruction, nontemporal like the results: a few tokens
-      // on many experts write mostly zeros, and temporal ones push the weights out of the last-level cache (13 tokens,
-      // 32 experts of 2944 x 1344: the next forward's up-projection 100 us against 65, the step 512 against 488).
-      const int col = cur.n0 + (lane & 31) * 8;
-#pragma unroll 4
-      for (int it = 0; it < BM / 16; ++it) {
-        const int row = cur.m0 + wave * (BM / 8) + it * 2 + (lane >> 5);
-        if (row < cur.m_end && col < p.N)
-          __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, reinterpret_cast<u32x4*>(y + (int64_t)row * p.ldy + col));
-      }
+      store_zero_tile<BM>(y, p.ldy, cur.m0, cur.m_end, cur.n0, p.N, wave, lane);
     } else {
 #pragma unroll
       for (int a = 0; a < FM; ++a)

@@ -113,4 +113,17 @@ inline Tile bwd_rows_tile(int cus, int64_t groups, int64_t rows_hint, int64_t ma
   return c256x128 < c256 ? TILE_256X128 : TILE_256X256;
 }
 
+// Weight gradients over segments of about rows_hint rows (0: unknown) into rows of `pitch` bf16 values: true = the
+// ring kernel's 256 x 256 tiles, false = the phase kernel's.  A tile of one or two K slices is bound by its stores.  The
+// ring kernel's waves write 256-byte row pieces, the phase kernel's 128-byte ones, which on rows that do not
+// start on a 128-byte line are two part lines each.  dW2 + dW13, us, ring / phase (F = 1024; 96 experts, or 64 at
+// 32, 40 and 144 rows):
+//   rows                     16       32       40       51       100      144      180      256
+//   d = 2560 (whole lines)   303/281  206/206  212/219  336/341  443/466  366/335  570/505  675/600
+//   d = 2528                 312/332  215/227  224/233  360/369  470/502  371/347  584/551  703/638
+//   d = 2552                 466/574  307/386  305/391  433/587  475/555  389/390  601/592  732/676
+inline bool wgrad_on_ring(int64_t rows_hint, int64_t pitch) {
+  return rows_hint > 0 && rows_hint <= 128 && (pitch % 64 != 0 || rows_hint > 32);
+}
+
 }  // namespace moe

@@ -115,14 +115,14 @@ def test_reload_finder():
 
 
 def test_weight_gradients_are_stored_nontemporally(device_asm):
-    """Every 16-byte store of the large-tile weight-gradient kernel, an empty group's zeros too: they are written
-    once and not read again by the step, and must not displace its weights in the last-level cache."""
+    """The results of the large-tile weight-gradient kernel, and an empty group's zeros where rows are whole lines: they
+    are written once and not read again by the step, and must not displace its weights in the last-level cache.
+    Only the zeros of other rows (one loop of four stores) are temporal."""
     f = [f for f in re.split(r"\n(?=_Z\S+:)", device_asm["gemm_bwd.hip"])
          if "k_phase_bwdILi256ELi1E" in f.split(":", 1)[0] and "v_mfma" in f]
     assert len(f) == 1
-    stores = [l.strip() for l in f[0].split("\n") if "global_store_dwordx4" in l]
-    assert len(stores) >= 17
-    assert not [l for l in stores if not re.search(r"\bnt\b", l)]
+    stores = [bool(re.search(r"\bnt\b", l)) for l in f[0].split("\n") if "global_store_dwordx4" in l]
+    assert sum(stores) >= 16 + 4 and len(stores) - sum(stores) <= 4, stores
 
 
 def _m0_hazards(lines):

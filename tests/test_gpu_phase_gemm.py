@@ -90,7 +90,22 @@ def test_backward_slice_counts_between_tiles(rows_hint, d, F, tile):
     edges cut tiles in both directions, and the row products' reductions end in a partial slice; the second case's
     dX runs on 320-row tiles (which take no partial slice).  Each
     gradient within rel. Frobenius 5e-3 (bf16 results of at most two bf16 intermediates)."""
-    counts = BACKWARD_COUNTS
+    _check_backward(BACKWARD_COUNTS, rows_hint, d, F)
+
+
+# (capacity per expert, d, F): short segments into rows of whole and of part lines
+SHORT = [(20, 512, 256), (60, 512, 256), (20, 520, 264), (120, 520, 264)]
+
+
+@pytest.mark.parametrize("rows_hint, d, F", SHORT)
+def test_backward_of_short_segments(rows_hint, d, F):
+    """The same on segments of at most two slices, empty ones among them, whose weight gradients run on the ring kernel
+    or the phase kernel (test_tile_rule.py checks that both do)."""
+    counts = [min(c, rows_hint * 3 // 2) for c in [0, 1, 7, 8, 0, 63, 64, 65, 31, 33, 127, 128]] * 9
+    _check_backward(counts, rows_hint, d, F)
+
+
+def _check_backward(counts, rows_hint, d, F):
     E = len(counts)
     sh = wl.MoEShape(T=rows_hint * E, d=d, E=E, top_k=1, F=F, E_local=E)
     offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)

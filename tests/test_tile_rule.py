@@ -28,6 +28,7 @@ def rule(tmp_path_factory):
     i, l = ctypes.c_int, ctypes.c_long
     lib.fwd_tile.argtypes = [i, i, i, l, l, l, i]
     lib.bwd_rows_tile.argtypes = [i, l, l, l, i, i]
+    lib.wgrad_on_ring.argtypes = [l, l]
     return lib
 
 
@@ -70,3 +71,18 @@ def test_a_partial_slice_keeps_the_tile(rule):
             tiles = {TILES[rule.fwd_tile(CUS, N, K, E, rows, 0, epilogue)] for K in (2040, 2048, 2056)}
             assert len(tiles) == 1, (E, rows, N, epilogue, tiles)
     assert TILES[rule.fwd_tile(CUS, 2040, 2040, 32, 256, 0, BF16)] == "320x256"
+
+
+def test_short_weight_gradients_stay_on_the_ring_kernel(rule):
+    """One and two K slices: except for a handful of rows into whole lines."""
+    for rows in (1, 16, 32):
+        assert not rule.wgrad_on_ring(rows, 2560) and rule.wgrad_on_ring(rows, 2528) and rule.wgrad_on_ring(rows, 2552)
+    for rows in (33, 64, 100, 128):
+        assert all(rule.wgrad_on_ring(rows, pitch) for pitch in (2560, 2528, 2552))
+    for rows in (0, 129, 256, 4000):
+        assert not any(rule.wgrad_on_ring(rows, pitch) for pitch in (2560, 2528, 2552))
+
+
+def test_short_backward_cases_reach_both_kernels(rule):
+    on_ring = {(bool(rule.wgrad_on_ring(rows, d)), d % 64 == 0) for rows, d, F in phase.SHORT}
+    assert on_ring == {(False, True), (True, True), (True, False)}

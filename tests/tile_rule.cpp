@@ -8,4 +8,5 @@ int fwd_tile(int cus, int N, int K, long groups, long rows_hint, long rows2, int
 int bwd_rows_tile(int cus, long groups, long rows_hint, long max_rows, int N, int K) {
   return moe::bwd_rows_tile(cus, groups, rows_hint, max_rows, N, K);
 }
+int wgrad_on_ring(long rows_hint, long pitch) { return moe::wgrad_on_ring(rows_hint, pitch); }
 }
