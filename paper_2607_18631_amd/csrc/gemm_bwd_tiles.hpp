@@ -5,6 +5,7 @@
 #include "common.hpp"
 #include "gemm_device.hpp"
 #include "kernels.hpp"
+#include "tile_rule.hpp"
 
 namespace moe {
 
@@ -86,11 +87,10 @@ __device__ __forceinline__ BTile bwd_decode(const GemmBwdProblem& p, int tile, i
     const int tm = (p.M + BM - 1) / BM;
     t.g = tile / (tm * tn);
     const int local = tile - t.g * tm * tn;
-    // n-fastest: the tiles an XCD runs together store whole output rows (32 experts of 255 rows, d = 7168,
-    // F = 2048: dW13 785 us m-fastest, 739 in blocks of 4 x 8 tiles, 720 n-fastest)
-    t.m0 = (local / tn) * BM;
+    const TileMN o = wgrad_order(local, tm, tn, p.Yf != nullptr);
+    t.m0 = o.m * BM;
     t.m_end = p.M;
-    t.n0 = (local % tn) * BN;
+    t.n0 = o.n * BN;
     t.kbeg = __builtin_amdgcn_readfirstlane(s_off[t.g]);
     t.klen = __builtin_amdgcn_readfirstlane(s_len[t.g]);
   }

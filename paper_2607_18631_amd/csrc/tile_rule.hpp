@@ -126,4 +126,15 @@ inline bool wgrad_on_ring(int64_t rows_hint, int64_t pitch) {
   return rows_hint > 0 && rows_hint <= 128 && (pitch % 64 != 0 || rows_hint > 32);
 }
 
+// Order of a weight gradient's tm x tn tiles.  bf16 results n-fastest: the tiles an XCD runs together store whole output rows
+// (32 experts of 255 rows, d = 7168, F = 2048: dW13 785 us m-fastest, 739 in blocks of 4 x 8 tiles, 720
+// n-fastest; the ring kernel, 96 experts of 51 rows, d = 2560, F = 1024: 239 and 215).  The router's float32 partials m-fastest, its
+// few m-tiles on one panel of the tokens (E = 384, T = 4096, d = 7168: 54.2 us, n-fastest 56.4; E = 256, T = 8192: 62.5, 63.6).
+struct TileMN {
+  int m, n;
+};
+constexpr TileMN wgrad_order(int i, int tm, int tn, bool f32) {
+  return f32 ? TileMN{i % tm, i / tm} : TileMN{i / tn, i % tn};
+}
+
 }  // namespace moe

@@ -86,3 +86,16 @@ def test_short_weight_gradients_stay_on_the_ring_kernel(rule):
 def test_short_backward_cases_reach_both_kernels(rule):
     on_ring = {(bool(rule.wgrad_on_ring(rows, d)), d % 64 == 0) for rows, d, F in phase.SHORT}
     assert on_ring == {(False, True), (True, True), (True, False)}
+
+
+@pytest.mark.parametrize("tm, tn", [(1, 1), (2, 56), (3, 14), (56, 16), (7, 1)])
+def test_weight_gradient_orders(rule, tm, tn):
+    """Each visits every tile once; the router's m-fastest, the others n-fastest."""
+    mn = (ctypes.c_int * 2)()
+    for f32 in (0, 1):
+        seen = []
+        for i in range(tm * tn):
+            rule.wgrad_order(i, tm, tn, f32, mn)
+            seen.append((mn[0], mn[1]))
+        assert seen == ([(m, n) for n in range(tn) for m in range(tm)] if f32 else
+                        [(m, n) for m in range(tm) for n in range(tn)])

@@ -8,5 +8,10 @@ int fwd_tile(int cus, int N, int K, long groups, long rows_hint, long rows2, int
 int bwd_rows_tile(int cus, long groups, long rows_hint, long max_rows, int N, int K) {
   return moe::bwd_rows_tile(cus, groups, rows_hint, max_rows, N, K);
 }
+void wgrad_order(int i, int tm, int tn, int f32, int* mn) {
+  const moe::TileMN o = moe::wgrad_order(i, tm, tn, f32);
+  mn[0] = o.m;
+  mn[1] = o.n;
+}
 int wgrad_on_ring(long rows_hint, long pitch) { return moe::wgrad_on_ring(rows_hint, pitch); }
 }
