@@ -235,8 +235,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_bwd(GemmBwdProblem
   // sync_slice(i): slice i landed for every wave and every wave is done reading slice i - 1's
   // slot, which then takes slice i + STAGES - 1 (a partial last slice is zeroed past the K
   // range).  Slices issued after slice i may stay in flight, except on a tile's first slice:
-  // the previous tile's result stores are queued behind its copies then, and loads and stores
-  // are not assumed to complete in order, so everything is drained.
+  // the previous tile's result stores are queued behind its copies then, an uncounted number, so
+  // everything is drained.
   constexpr int L = CX::L + CW::L;                       // copy instructions per slice and wave
   auto sync_slice = [&](int i) {
     const int after = min(STAGES - 2, nl - 1 - i);

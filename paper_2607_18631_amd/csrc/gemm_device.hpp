@@ -8,6 +8,9 @@
 
 namespace moe {
 
+// Wait until at most N vector-memory operations of the wave are in flight.  The counter falls in issue order on this
+// architecture, loads, direct-to-LDS copies and stores alike (the CDNA instruction set documents: memory reads and writes return in the
+// order they were issued), so the N youngest may be of any kind.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");

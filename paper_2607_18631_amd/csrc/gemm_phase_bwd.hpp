@@ -10,8 +10,8 @@
 //    copy latency.
 //  - routed dW13 880 -> 720, dW2 445 -> 390 (14336 tiles of 4-5 slices each, 128 KB of results per tile).
 //    The next tile's first two slices stream in behind the last two of this one, and its first slice runs
-//    over the stores still in flight; without any store the launch takes 516 us, and the stores, 1.9 GB at
-//    about 7 TB/s, come on top: loads wait behind stores in the same in-order counter.
+//    over the stores still in flight.  Without any store the launch takes 516 us: the stores, 1.9 GB, add 204, as loads
+//    wait behind stores in the same in-order counter.  At most two slices per group: the ring kernel's (wgrad_on_ring).
 //  - shared dW13 463 -> 417, dW2 218 -> 209 (K = 8192).
 #pragma once
 #include <type_traits>
@@ -92,6 +92,8 @@ __global__ __launch_bounds__(512, 1) void k_phase_bwd(GemmBwdProblem p) {
   constexpr bool KSEG = MODE == BWD_KSEG;
   using PT = PhaseTile<BM, KSEG, true, false>;
   constexpr int BN = PT::BN, BK = PT::BK, FM = PT::FM, NTH = 512;
+  constexpr int SPB = kStoresPerBlock;
+  static_assert(!KSEG || BM / 16 == FM * SPB, "store_zero_tile leaves as many stores as a full tile's results");
   extern __shared__ __align__(16) uint8_t smem[];
   bf16_t* ring = reinterpret_cast<bf16_t*>(smem);          // [2][SLICE]
   __shared__ int s_off[kMaxGroups];
@@ -172,8 +174,8 @@ __global__ __launch_bounds__(512, 1) void k_phase_bwd(GemmBwdProblem p) {
         cp.wnext = wptr(td);
         cp.xlast_next = xend(td);
         cp.wlast_next = wend(td);
-        phase_wait_first<FM, 4, PT>(nl, nst);
-        phase_loop<FM, FM, KTAIL, false, FM * 4, true>(pt, cp, acc, nl, cur.klen, s0, stream);
+        phase_wait_first<FM, SPB, PT>(nl, nst);
+        phase_loop<FM, FM, KTAIL, false, FM * SPB, true>(pt, cp, acc, nl, cur.klen, s0, stream);
         if (stream) {
           cp.xbase = cp.xnext;
           cp.wbase = cp.wnext;
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(512, 1) void k_phase_bwd(GemmBwdProblem p) {
       const int na = __builtin_amdgcn_readfirstlane(max(0, (live - wm + 1) / 2));   // live blocks of this wave
       with_phases<FM>(phases(cur), [&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        phase_wait_first<P, 4, PT>(nl, nst);
+        phase_wait_first<P, SPB, PT>(nl, nst);
         if (na >= P) phase_loop<P, P, KTAIL, false, 0, false>(pt, cp, acc, nl, cur.klen);
         else if (P > 2 || na == 1) phase_loop<P, P - 1, KTAIL, false, 0, false>(pt, cp, acc, nl, cur.klen);
         else if constexpr (P == 2) phase_loop<P, 0, KTAIL, false, 0, false>(pt, cp, acc, nl, cur.klen);
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(512, 1) void k_phase_bwd(GemmBwdProblem p) {
       for (int a = 0; a < FM; ++a)
         if (row0 + a * 64 < cur.m_end) store_block<KSEG>(acc[a], y, p.ldy, row0 + a * 64, cur.m_end, col0, p.N, lane);
     }
-    // at least four stores for each 32-row block that lies inside the output (K segments: the first slice
+    // at least SPB stores for each 32-row block that lies inside the output (K segments: the first slice
     // counts on all of a full tile's, so an edge tile leaves nothing in flight)
     nst = col0 + 64 > p.N ? 0 : max(0, min(FM, (cur.m_end - row0 + 32) / 64));
     if (KSEG && !full(cur)) {

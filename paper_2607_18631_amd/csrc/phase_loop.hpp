@@ -323,6 +323,9 @@ __device__ __forceinline__ int pair_dst(int lane) {
   return ((lane & 15) * 4 + (q & 1) * 2 + (q >> 1)) * 4;
 }
 
+// Stores of store_block for a block inside its bounds: what a wait may count on behind the copies before it.
+constexpr int kStoresPerBlock = 4;
+
 // Store 16 bytes at a wave-uniform base plus the lane's 32-bit byte offset.
 template <bool NT>
 __device__ __forceinline__ void st16_at(char* base, uint32_t off, u32x4 v) {
@@ -332,7 +335,7 @@ __device__ __forceinline__ void st16_at(char* base, uint32_t off, u32x4 v) {
 }
 
 // The bf16 results of one 32-row x 64-column block (acc[r][b]) to rows rbase .. of Y, columns col0 ..; rows
-// from row_end and columns from ncol on are not stored.  A block inside both costs exactly four stores.
+// from row_end and columns from ncol on are not stored.  A block inside both costs exactly kStoresPerBlock stores.
 template <bool NT>
 __device__ __forceinline__ void store_block(const f32x4 (&acc)[2][4], bf16_t* Y, int64_t ld, int rbase, int row_end,
                                             int col0, int ncol, int lane) {
@@ -341,6 +344,7 @@ __device__ __forceinline__ void store_block(const f32x4 (&acc)[2][4], bf16_t* Y,
   const uint32_t off = (lr * (uint32_t)ld + lc) * 2;
   const int src = line_src(lane);
   const bool full = rbase + 32 <= row_end && col0 + 64 <= ncol;
+  static_assert(kStoresPerBlock == 2 * 2, "row halves x line halves below");
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     u32x4 v[2] = {pack_pieces(acc[r][0], acc[r][1]), pack_pieces(acc[r][2], acc[r][3])};

@@ -45,16 +45,15 @@ inline Tile fwd_tile(const FwdSizes& s, FwdEpilogue epi) {
                     : s.rows_hint <= 512              ? TILE_128X256
                                                       : TILE_256X256;
   if (tier == TILE_64X128 || s.rows_hint <= 0 || epi == FWD_SCATTER) return tier;
-  // Tile shape from the expected tile count of each shape.  A persistent launch takes about
-  // ceil(tiles / CUs) rounds of its slowest workgroup; per tile, a 320 x 256 tile (10 token
-  // blocks, 2 x 4 waves) costs ~1.15 of a 256 x 256 one, a 128 x 256 tile ~0.7, a 256 x 128 tile
-  // ~0.6 (measured).  DeepSeek-V3 shapes (256 rows per expert,
-  // shared expert of 8192 rows in the launch) run both projections on 320-row tiles (up
-  // 1085-1093 -> 1000-1025 us, down 588-596 -> 565-568), Mixtral shapes (1024 rows per expert,
-  // 2.25 rounds of 256 x 256 down-projection tiles) their down-projection (1137-1147 -> 944-955;
-  // 256 x 128 tiles: 1097), while Mixtral's up-projection (15.75 rounds either way) and the
-  // skewed workload stay on 256 x 256.  The backward's recomputed up-projection of the routed
-  // experts alone (tier 128 x 256) takes 320-row tiles at DeepSeek-V3 (627 -> 521 us).
+  // Tile shape from the expected tile count of each shape.  A persistent launch takes about ceil(tiles / CUs) rounds of
+  // its slowest workgroup.  A round of each tile against one of 256 x 256, measured over whole rounds of full tiles (K =
+  // 1024 to 7168, 1 to 7 rounds, both epilogues): 320 x 256 1.07-1.17 (priced 1.15), 256 x 128 0.53-0.63 (priced 0.6), 128 x 256
+  // 0.71-0.94.  The last is priced 0.7, its cost when the 256 x 256 tile was 10-15% slower; the choices that follow
+  // from it were checked at the sizes below.  DeepSeek-V3 shapes (256 rows per expert, shared expert of 8192 rows
+  // in the launch) run both projections on 320-row tiles, Mixtral shapes (1024 rows per expert, 2.25 rounds of 256 x 256
+  // down-projection tiles) their down-projection, while Mixtral's up-projection (15.75 rounds either way) and the skewed
+  // workload stay on 256 x 256.  Up-projections on 320-row tiles against 128 x 256 ones: 32 experts of 290 rows, d = 6384, F =
+  // 4104 1147 us and 1607; 64 of 227, d = 3184, F = 4688 1133 and 1352; 32 of 320, d = 6160, F = 600 236 and 269.
   auto mtiles = [&](int bm) {
     return expected_mtiles(bm, (double)s.rows_hint, s.groups) + std::ceil((double)s.rows2 / bm);
   };
@@ -64,8 +63,12 @@ inline Tile fwd_tile(const FwdSizes& s, FwdEpilogue epi) {
   const double tn = epi == FWD_SWIGLU ? tn128 : std::ceil(tn128 / 2);
   const double m128 = mtiles(128), m256 = mtiles(256), m320 = mtiles(320);
   // A launch whose 256-row tiles cover at most a quarter of the chip takes 64 x 128 ones, an eighth of
-  // the work each and two workgroups per CU, so they still fit about one round.  3001 rows x a
-  // shared expert of F = 264, d = 2040: up-projection 36 tiles of 256 x 256 109 us, 235 of 64 x 128 26 us.
+  // the work each and two workgroups per CU, so they still fit about one round.  One segment, us on 256 x 256 / 64 x 128, by
+  // tiles of 256 x 256 (of 256 CUs), up-projection and down-projection:
+  //   tiles                 16         32         64         96         128        256
+  //   up, K = 2048          41/18      42/19      42/31      43/44      45/54      55/105
+  //   up, K = 7168          121/45     122/49     122/104    126/130    135/177    175/351
+  //   down, K = 1024        24/11      24/12      25/19      26/26      27/32      33/58
   if (tier == TILE_256X256 && s.rows2 == 0 && m256 * tn <= s.cus / 4.0) return TILE_64X128;
   // With a partial last K slice too: 32 experts of 256 rows, d = F = 2040: up-projection 174 us on 320-row tiles, 274 on
   // 128 x 256, down-projection 96 and 152; 8 experts of 569 rows, d = 6408, F = 6112: up 633 and 842 (256 x 256), down 355 and 408.
@@ -99,8 +102,9 @@ inline int extra_group_rows(const FwdSizes& s, FwdEpilogue epi, Tile tile) {
 // reads four token fragments (ds_read_b128) and two weight fragments, against two and four
 // with 4 x 2 waves -- the transpose reads are the dearer ones (DeepSeek-V3 routed dX 816 ->
 // 634 us, shared dX 605 -> 481); 256 x 128 (4 x 2 waves); 320 x 256 (2 x 4 waves, 10 token
-// blocks).  Chosen like the forward's tiles, from the expected tile count of each shape; no 320-row
-// tiles with a K tail.
+// blocks).  Chosen like the forward's tiles, from the expected tile count of each shape; a round of 320 x 256 against
+// one of 256 x 256 measured 1.08-1.23 (priced 1.15), 256 x 128 0.55-0.65 (priced 0.6).  No 320-row tiles with a
+// K tail: no instance of the kernel (its registers do not suffice).
 inline Tile bwd_rows_tile(int cus, int64_t groups, int64_t rows_hint, int64_t max_rows, int N, int K) {
   if (rows_hint > 0 && rows_hint <= 128) return TILE_64X128;
   const double rows = rows_hint > 0 ? (double)rows_hint : (double)max_rows / groups;
