@@ -81,14 +81,24 @@ def gating_desc(sh):
 
 
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "gemm_swiglu_dsv3_traffic.md")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2607_18631_amd", "csrc", "gemm.hip")
+# the sources that decide the launch's kernel, tiles and copies
+GEMM_SOURCES = [os.path.join(ROOT, "paper_2607_18631_amd", "csrc", f) for f in
+                ("gemm.hip", "gemm_phase.hip", "gemm_tiles.hpp", "gemm_device.hpp", "phase_loop.hpp", "tile_rule.hpp")]
+
+
+def gemm_sources_sha256():
+    import hashlib
+    h = hashlib.sha256()
+    for path in GEMM_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic(workload):
     """HBM bytes per launch of the SwiGLU GEMM from the committed rocprofv3 FETCH_SIZE / WRITE_SIZE
-    summary, or None when the kernel source changed since the counters were taken (or another
+    summary, or None when the kernel's sources changed since the counters were taken (or another
     workload is benchmarked)."""
-    import hashlib
     if workload != "dsv3" or not os.path.exists(TRAFFIC_SUMMARY):
         return None
     fields = {}
@@ -98,9 +108,7 @@ def measured_traffic(workload):
             if ":" in line and line.startswith(("traffic_bytes_per_launch", "kernel_source_sha256")):
                 k, v = line.split(":", 1)
                 fields[k.strip()] = v.strip()
-    with open(GEMM_SOURCE, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()
-    if fields.get("kernel_source_sha256") != sha or "traffic_bytes_per_launch" not in fields:
+    if fields.get("kernel_source_sha256") != gemm_sources_sha256() or "traffic_bytes_per_launch" not in fields:
         return None
     return float(fields["traffic_bytes_per_launch"])
 
@@ -154,7 +162,7 @@ class ReadProbe:
         self.lib.probe_read_stream.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
         self.lib.probe_read_sink_words.restype = ctypes.c_int64
         self.sink = torch.empty(int(self.lib.probe_read_sink_words()), dtype=torch.int32, device="cuda:0")
-        self.lib.probe_mfma_loop.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+        self.lib.probe_mfma_loop.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
         self.lib.probe_mfma_blocks.restype = ctypes.c_int64
         self.lib.probe_mfma_flops.argtypes = [ctypes.c_int]
         self.lib.probe_mfma_flops.restype = ctypes.c_double
@@ -172,13 +180,13 @@ class ReadProbe:
         if rc != 0:
             raise RuntimeError(f"probe_read_stream failed ({rc})")
 
-    def mfma(self, iters):
-        """One launch of the MFMA loop probe; returns its flops."""
+    def mfma(self, iters, small=0):
+        """One launch of the MFMA loop probe (32 x 32 x 16, or 16 x 16 x 32 MFMAs); returns its flops."""
         import torch
         if self.mfma_sink is None:
             self.mfma_sink = torch.empty(int(self.lib.probe_mfma_blocks()) * 256, dtype=torch.float32,
                                          device="cuda:0")
-        rc = self.lib.probe_mfma_loop(iters, self.mfma_sink.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        rc = self.lib.probe_mfma_loop(iters, small, self.mfma_sink.data_ptr(), torch.cuda.current_stream().cuda_stream)
         if rc != 0:
             raise RuntimeError(f"probe_mfma_loop failed ({rc})")
         return self.lib.probe_mfma_flops(iters)
@@ -732,6 +740,8 @@ def main():
     mfma_iters = 20000
     mfma_ms = timed_median(lambda: probe.mfma(mfma_iters), 5, warmup=2)
     mfma_tflops = probe.lib.probe_mfma_flops(mfma_iters) / (mfma_ms * 1e-3) / 1e12
+    mfma16_ms = timed_median(lambda: probe.mfma(mfma_iters, 1), 5, warmup=2)
+    mfma16_tflops = probe.lib.probe_mfma_flops(mfma_iters) / (mfma16_ms * 1e-3) / 1e12
     # LDS read ceiling: ds_read_b128 streams from LDS on every SIMD (2 waves each)
     log("timing the LDS read probe")
     lds_iters = 10000
@@ -929,6 +939,7 @@ def main():
         "fill_gbs": (1 << 30) / (fill_ms * 1e-3) / 1e9,
         "mfma_loop_tflops": mfma_tflops,
         "mfma_loop_clock_ghz": mfma_tflops / PEAK_BF16_TFLOPS * 2.4,
+        "mfma16_loop_tflops": mfma16_tflops,
         "lds_read_tbs": lds_tbs,
         "lds_read_bytes_per_clk_cu": lds_tbs * 1e12 / (256 * lds_clock * 1e9),
         "lds_probe_clock_ghz": lds_clock,
@@ -937,7 +948,7 @@ def main():
         "step_ms": {n: round(float(step_med[i]), 5) for n, i in s.items()},
         "gpu_event_ms_per_step": float(per_call.mean()),
         "roofline": {
-            "kernel": "k_grouped_gemm<EPI_SWIGLU> (W1/W3 GEMM + SwiGLU of the routed experts and the shared expert)",
+            "kernel": "SwiGLU up-projection, k_phase_gemm<EPI_SWIGLU> on 256- and 320-row tiles, else k_grouped_gemm (W1/W3 GEMM + SwiGLU of the routed experts and the shared expert)",
             "bound": "mfma",
             "achieved": achieved,
             "peak": PEAK_BF16_TFLOPS,

@@ -4,10 +4,10 @@
 //
 // What bounds these tiles is power and the latency of the slice copies, and the kernel is built
 // around both (measured on 8192 x 4096 x 7168, one group, random data, back to back):
-//  - MFMA shape.  A register-only loop of 16 x 16 x 32 MFMAs on random operands sustains 2050-2100
-//    TFLOP/s at 2.0-2.08 GHz, the same loop of 32 x 32 x 16 ones 1815-1830 at 1.8 GHz: under full
-//    matrix load the clock is what the power limit leaves, and the smaller shape takes less power
-//    per flop.  Keeping the weight operand over two consecutive MFMAs takes 2% less than keeping
+//  - MFMA shape.  A register-only loop of 16 x 16 x 32 MFMAs (probe/stream.hip, operands of 8 random bits)
+//    sustains 2330 TFLOP/s, the same loop of 32 x 32 x 16 ones 1905 (with all mantissa bits random 2050-2100 and
+//    1815-1830): under full matrix load the clock is what the power limit leaves, and the smaller shape takes
+//    less power per flop.  Keeping the weight operand over two consecutive MFMAs takes 2% less than keeping
 //    the token operand.
 //  - Copy lead.  With a K slice consumed K-step by K-step, its LDS slot is busy until the last
 //    step, and a copy has one slice (~1.1 us) to land, less than the latency past the L2.  Here a
@@ -21,8 +21,8 @@
 //    waiting for LDS at every barrier (301,500 cycles per 112-slice tile against 270,000; 229,400
 //    is the MFMAs alone).
 // Up-projection of the benchmark's layer (8192 tokens, d = 7168, 32 experts and a shared one of
-// F = 2048) 845 -> 765 us, down-projection 465 -> 420; 4096 tokens x 8 experts of 14336 wide: 1600 ->
-// 1500 and 812 -> 778; the single group above 1347 -> 1450 TFLOP/s.
+// F = 2048) 845 -> 750 us, down-projection 465 -> 410; 4096 tokens x 8 experts of 14336 wide: 1600 ->
+// 1495 and 812 -> 765; the single group above 1347 -> 1450 TFLOP/s.
 #include <type_traits>
 
 #include "common.hpp"

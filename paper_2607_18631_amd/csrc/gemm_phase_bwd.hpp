@@ -6,13 +6,13 @@
 //
 // What bounds them, and what was measured (8192 tokens, d = 7168, 32 experts and a shared one of F = 2048;
 // before: 32 x 32 x 16 MFMAs, one slice of copy lead, results staged in LDS):
-//  - routed dX 537 -> 489 us, dA 264 -> 232, shared dX 416 -> 354, dA 219 -> 173: as the forward, power and
+//  - routed dX 503 -> 456 us, dA 275 -> 228, shared dX 409 -> 359, dA 218 -> 180: as the forward, power and
 //    copy latency.
-//  - routed dW13 880 -> 720, dW2 445 -> 390 (14336 tiles of 4-5 slices each, 128 KB of results per tile).
+//  - routed dW13 853 -> 683, dW2 430 -> 370 (14336 tiles of 4-5 slices each, 128 KB of results per tile).
 //    The next tile's first two slices stream in behind the last two of this one, and its first slice runs
 //    over the stores still in flight.  Without any store the launch takes 516 us: the stores, 1.9 GB, add 204, as loads
 //    wait behind stores in the same in-order counter.  At most two slices per group: the ring kernel's (wgrad_on_ring).
-//  - shared dW13 463 -> 417, dW2 218 -> 209 (K = 8192).
+//  - shared dW13 454 -> 434, dW2 221 -> 214 (K = 8192).
 #pragma once
 #include <type_traits>
 

@@ -35,10 +35,13 @@ __global__ __launch_bounds__(256) void k_read_stream(const u32x4* src, int64_t n
 constexpr int kMfmaChains = 4;         // independent accumulators per wave
 constexpr int kMfmaBlocks = 256 * 2;   // two workgroups of 4 waves per compute unit (2 waves per SIMD)
 
-// Each wave issues iters x kMfmaChains v_mfma_f32_32x32x16_bf16 on fixed register operands (bf16
-// values from a hash of the lane, so the multipliers see varied data), then stores one float per
-// lane so that the loop is kept.
+// Each wave issues iters x kMfmaChains v_mfma_f32_32x32x16_bf16, or twice as many v_mfma_f32_16x16x32_bf16 of
+// half the flop each (SMALL), on fixed register operands (bf16 values from a hash of the lane, so the multipliers
+// see varied data), then stores one float per lane so that the loop is kept.
+template <bool SMALL>
 __global__ __launch_bounds__(256) void k_mfma_loop(int iters, float* sink) {
+  constexpr int CHAINS = SMALL ? 2 * kMfmaChains : kMfmaChains, REGS = SMALL ? 4 : 16;
+  typedef float acc_t __attribute__((ext_vector_type(REGS)));
   const uint32_t lane = threadIdx.x;
   bf16x8 a, b;
 #pragma unroll
@@ -47,20 +50,29 @@ __global__ __launch_bounds__(256) void k_mfma_loop(int iters, float* sink) {
     a[i] = (__bf16)((float)((h >> 8) & 0xff) * (1.0f / 256.0f) - 0.5f);
     b[i] = (__bf16)((float)((h >> 16) & 0xff) * (1.0f / 256.0f) - 0.5f);
   }
-  f32x16 acc[kMfmaChains];
+  acc_t acc[CHAINS];
 #pragma unroll
-  for (int c = 0; c < kMfmaChains; ++c)
+  for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[c][i] = 0.f;
+    for (int i = 0; i < REGS; ++i) acc[c][i] = 0.f;
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int c = 0; c < kMfmaChains; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[c], 0, 0, 0);
+    for (int c = 0; c < CHAINS; ++c) {
+      // asm: the compiler's own loop copies accumulators between MFMAs
+      if constexpr (SMALL) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[c]) : "v"(a), "v"(b));
+      else acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[c], 0, 0, 0);
+    }
+  }
+  // the compiler does not see when the asm's results are ready
+  if constexpr (SMALL) {
+#pragma unroll
+    for (int c = 0; c < CHAINS; ++c) asm volatile("s_nop 15" : "+v"(acc[c]));
   }
   float r = 0.f;
 #pragma unroll
-  for (int c = 0; c < kMfmaChains; ++c)
+  for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) r += acc[c][i];
+    for (int i = 0; i < REGS; ++i) r += acc[c][i];
   sink[(int64_t)blockIdx.x * blockDim.x + threadIdx.x] = r;
 }
 
@@ -136,11 +148,12 @@ extern "C" int probe_read_stream(const void* src, int64_t bytes, void* sink, voi
 extern "C" int64_t probe_read_sink_words(void) { return 256 * 8 * 4; }
 
 // Runs the MFMA loop: probe_mfma_blocks() workgroups of 256 threads, each wave issuing iters x 4
-// MFMAs of 32 x 32 x 16 (32,768 flop each); `sink` holds probe_mfma_blocks() * 256 floats.
-// Returns a hipError_t.
-extern "C" int probe_mfma_loop(int iters, void* sink, void* stream) {
+// MFMAs of 32 x 32 x 16 (32,768 flop each) or, with `small` set, iters x 8 of 16 x 16 x 32 (16,384 flop
+// each); `sink` holds probe_mfma_blocks() * 256 floats.  Returns a hipError_t.
+extern "C" int probe_mfma_loop(int iters, int small, void* sink, void* stream) {
   if (!sink || iters < 1) return (int)hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_mfma_loop, dim3(kMfmaBlocks), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), iters,
+  const auto fn = small ? k_mfma_loop<true> : k_mfma_loop<false>;
+  hipLaunchKernelGGL(fn, dim3(kMfmaBlocks), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), iters,
                      static_cast<float*>(sink));
   return (int)hipGetLastError();
 }
