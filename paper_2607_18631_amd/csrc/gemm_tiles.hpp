@@ -4,6 +4,7 @@
 #include "common.hpp"
 #include "gemm_device.hpp"
 #include "kernels.hpp"
+#include "tile_rule.hpp"
 
 namespace moe {
 
@@ -17,11 +18,6 @@ hipError_t launch_phase_gemm(int bm, const GemmProblem& p, hipStream_t stream);
 
 // epilogues whose weight tile pairs gate rows [0, N) with up rows [N, 2N)
 constexpr bool swiglu_pairs(int epi) { return epi == EPI_SWIGLU || epi == EPI_SWIGLU_BWD; }
-
-// m-tiles per band of the tile order: 4 against 8 measured 2% faster on the up-projection of 4096 tokens x 8
-// experts of 14336 (1450 -> 1421 us); 256 x 128 ring tiles, six down-projections of 1 to 8 segments of 2500 to
-// 6900 rows: within 1%, one 4% faster (59.8 us, 62.3 with 8)
-constexpr int BAND_M = 4;
 
 // ---------------------------------------------------------------------------------------
 // Tile table, tile decoding, slice copies, epilogue
@@ -180,13 +176,14 @@ __device__ __forceinline__ TileCode tile_code(const GemmProblem& p, const TileSp
   }
   const int bmg = extra ? ts.bmx : BM;                  // m-tile height of this group
   const int mt = (c.row_end - row0g + bmg - 1) / bmg;
-  // banded order: bands of up to BAND_M m-tiles; inside a band m-fastest, then n.  The
-  // 32 adjacent tiles one XCD runs at a time then share BAND_M token panels and
-  // 32 / BAND_M weight panels (groups with few m-tiles reduce to plain m-fastest order)
-  const int band = local / (BAND_M * ts.tiles_n);
-  const int bm0 = band * BAND_M;
-  const int bmt = min(BAND_M, mt - bm0);
-  const int in_band = local - band * BAND_M * ts.tiles_n;
+  constexpr int BAND = band_m(BM);
+  // banded order: bands of up to BAND m-tiles; inside a band m-fastest, then n.  The
+  // 32 adjacent tiles one XCD runs at a time then share BAND token panels and
+  // 32 / BAND weight panels (groups with few m-tiles reduce to plain m-fastest order)
+  const int band = local / (BAND * ts.tiles_n);
+  const int bm0 = band * BAND;
+  const int bmt = min(BAND, mt - bm0);
+  const int in_band = local - band * BAND * ts.tiles_n;
   const int mi = bm0 + in_band % bmt;
   c.ni = in_band / bmt;
   c.row0 = row0g + mi * bmg;

@@ -99,3 +99,10 @@ def test_weight_gradient_orders(rule, tm, tn):
             seen.append((mn[0], mn[1]))
         assert seen == ([(m, n) for n in range(tn) for m in range(tm)] if f32 else
                         [(m, n) for m in range(tm) for n in range(tn)])
+
+
+def test_bands_of_small_tiles_hold_a_shared_experts_rows(rule):
+    """Launches on 64- and 128-row tiles share their weights with a dense extra group of up to 512 rows; its weights are
+    streamed once per band."""
+    assert rule.band_m(64) * 64 >= 512 and rule.band_m(128) * 128 >= 512
+    assert rule.band_m(256) == rule.band_m(320) == 4

@@ -13,5 +13,6 @@ void wgrad_order(int i, int tm, int tn, int f32, int* mn) {
   mn[0] = o.m;
   mn[1] = o.n;
 }
+int band_m(int bm) { return moe::band_m(bm); }
 int wgrad_on_ring(long rows_hint, long pitch) { return moe::wgrad_on_ring(rows_hint, pitch); }
 }
