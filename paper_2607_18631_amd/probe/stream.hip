@@ -55,6 +55,11 @@ __global__ __launch_bounds__(256) void k_mfma_loop(int iters, float* sink) {
   for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
     for (int i = 0; i < REGS; ++i) acc[c][i] = 0.f;
+  // the compiler does not see that the asm below reads what vector instructions have just written
+  if constexpr (SMALL) {
+#pragma unroll
+    for (int c = 0; c < CHAINS; ++c) asm volatile("s_nop 1" : "+v"(acc[c]), "+v"(a), "+v"(b));
+  }
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
     for (int c = 0; c < CHAINS; ++c) {
